@@ -11,6 +11,10 @@
 // stand-alone argmax (larger value first, NaN above everything, -0 == +0,
 // lower id on ties), so the [rows, V] fp32 logits never exist in memory.
 //
+// Two kernels: up to 128 rows the call is a stream of the weight
+// (lm_head_stream_kernel, described there); more rows take a tiled matrix
+// product (lm_head_argmax_kernel):
+//
 //   * Workgroup tile: 256 vocabulary entries (MFMA M) x 256 hidden rows
 //     (MFMA N), the largest whose fp32 accumulators fit a CU's registers.
 //     Eight waves (two per SIMD, so one wave's waits are covered by the
@@ -69,6 +73,7 @@ constexpr int kFragM = kWaveM / 32, kFragN = kWaveN / 32;
 constexpr int kReads = kFragM + kFragN;                // fragment reads per K step
 constexpr int kSteps = kFragM * kFragN;                // MFMAs per K step
 constexpr int kPre = 2;                                // MFMAs before a hand-off
+constexpr int kStreamRows = 128;                       // most rows of lm_head_stream_kernel
 static_assert(kWLoads * kWaves * 8 == kTileM && kHLoads * kWaves * 16 == kTileN, "load blocks");
 static_assert(kWStages * kWUnitBytes + kHStages * kHSliceBytes <= 160 * 1024, "LDS");
 
@@ -109,6 +114,16 @@ __device__ __forceinline__ unsigned long long halves_max64(unsigned long long x)
     const unsigned lo = (unsigned)x, hi = (unsigned)(x >> 32);
     const auto l = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
     const auto h = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+    const unsigned long long a = ((unsigned long long)h[0] << 32) | l[0];
+    const unsigned long long b = ((unsigned long long)h[1] << 32) | l[1];
+    return umax64(a, b);
+}
+
+// Maximum of a 64-bit key held by lanes l and l ^ 16.
+__device__ __forceinline__ unsigned long long rows_max64(unsigned long long x) {
+    const unsigned lo = (unsigned)x, hi = (unsigned)(x >> 32);
+    const auto l = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+    const auto h = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
     const unsigned long long a = ((unsigned long long)h[0] << 32) | l[0];
     const unsigned long long b = ((unsigned long long)h[1] << 32) | l[1];
     return umax64(a, b);
@@ -377,6 +392,234 @@ __global__ __launch_bounds__(kLmThreads, 1) void lm_head_argmax_kernel(
     }
 }
 
+// ---------------------------------------------------------------------------
+// Few rows (R <= kStreamRows): the weight stream is the whole cost.
+//
+// The 256-row tile multiplies mostly padding here (24 rows: ten times the
+// matrix work they need) and leaves CUs without a tile at small vocabularies
+// (32000 entries: 125 of 256). Instead the vocabulary is cut into one equal
+// range of rows per workgroup; a workgroup walks its range in tiles of WV
+// waves x 16 MB rows, every wave with all hidden rows (NB blocks of 16) on
+// v_mfma_f32_16x16x32_bf16.
+//   * Weight and hidden units of 64 elements (whole 128-byte lines) stream into
+//     one S-stage LDS ring, S - 1 units in flight, one barrier per unit: a
+//     unit's matrix work is a fraction of the time its lines take to arrive.
+//     The ring does not drain between tiles. The weight is read once, so its
+//     loads are non-temporal and leave the L2 to the hidden rows, which every
+//     workgroup re-reads (64 rows over 128256 x 4096: 196 -> 180 us).
+//   * A wave whose rows of the range's last tile are all past the range's end
+//     neither loads nor multiplies.
+//   * The best key per hidden row stays in registers over the tiles: one atomic
+//     maximum per row and workgroup.
+// Every vocabulary row is summed in the same K order, so equal weight rows give
+// equal sums. Measured, this kernel against the 256-row tile (us, d = 4096):
+// 24 rows x 32000 entries 108 -> 47 (5.6 TB/s of weight), 64 x 128256
+// 269 -> 155 (6.8 TB/s), 64 x 50257 109 -> 77, 100 x 128256 266 -> 173.
+template <int NB, int MB, int S, int WV>
+__global__ __launch_bounds__(WV * kWave, 1) void lm_head_stream_kernel(
+    const uint16_t *__restrict__ hidden, const uint16_t *__restrict__ w, int R, int V, int d,
+    unsigned long long *__restrict__ keys) {
+    constexpr int kTM = WV * MB * 16;                    // vocabulary rows of a tile
+    constexpr int kHR = NB * 16 < WV * 8 ? WV * 8 : NB * 16;       // hidden rows staged
+    constexpr int kStage = (kTM + kHR) * kWRow;
+    constexpr int kWL = MB * 2;                          // 1 KB loads per wave and unit: weight,
+    constexpr int kHL = kHR / (WV * 8);                  // hidden
+    constexpr int kStreamed = 2;                         // cache policy: non-temporal
+    __shared__ __attribute__((aligned(1024))) unsigned char ring[S * kStage];
+
+    const int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int lane = tid & (kWave - 1);
+    const int U = d / kUnitK;
+    const int vbeg = (int)((long long)V * blockIdx.x / gridDim.x);
+    const int vend = (int)((long long)V * (blockIdx.x + 1) / gridDim.x);
+    const int total = (vend - vbeg + kTM - 1) / kTM * U; // units of this workgroup
+
+    // Load block i of a wave: 8 rows, lane p fills row p / 8, position p % 8,
+    // which holds chunk (p % 8) ^ ((row >> 1) & 7). Rows past the end of W or
+    // hidden read the last row (finite data; the results are discarded).
+    const char *hsrc[kHL];
+    #pragma unroll
+    for (int i = 0; i < kHL; ++i) {
+        const int row = (wave * kHL + i) * 8 + (lane >> 3);
+        hsrc[i] = reinterpret_cast<const char *>(hidden + (size_t)min(row, R - 1) * d) +
+                  (((lane & 7) ^ ((row >> 1) & 7)) << 4);
+    }
+    const char *wsrc[kWL];
+    bool iw;                                             // this wave has rows in the tile being loaded
+    auto set_tile = [&](int v0) {
+        iw = wave * MB * 16 < vend - v0;
+        #pragma unroll
+        for (int i = 0; i < kWL; ++i) {
+            const int row = (wave * kWL + i) * 8 + (lane >> 3);
+            wsrc[i] = reinterpret_cast<const char *>(w + (size_t)(v0 + min(row, vend - 1 - v0)) * d) +
+                      (((lane & 7) ^ ((row >> 1) & 7)) << 4);
+        }
+    };
+    int ik = 0, iv = vbeg, istage = 0;                   // next unit to load
+    set_tile(iv);
+    auto issue = [&]() {
+        unsigned char *st = ring + istage * kStage;
+        const size_t ko = (size_t)ik * kWRow;
+        if (iw) {
+            #pragma unroll
+            for (int i = 0; i < kWL; ++i)
+                __builtin_amdgcn_global_load_lds((const GLOBAL_AS void *)(wsrc[i] + ko),
+                                                 (LDS_AS void *)(st + (wave * kWL + i) * 1024),
+                                                 16, 0, kStreamed);
+        }
+        #pragma unroll
+        for (int i = 0; i < kHL; ++i)
+            __builtin_amdgcn_global_load_lds((const GLOBAL_AS void *)(hsrc[i] + ko),
+                                             (LDS_AS void *)(st + kTM * kWRow + (wave * kHL + i) * 1024),
+                                             16, 0, 0);
+        istage = istage == S - 1 ? 0 : istage + 1;
+        if (++ik == U) {
+            ik = 0;
+            iv += kTM;
+            set_tile(iv);
+        }
+    };
+    #pragma unroll
+    for (int x = 0; x < S - 1; ++x)
+        if (x < total) issue();
+
+    // Fragments of v_mfma_f32_16x16x32_bf16: lane l reads row l % 16 of a
+    // 16-row block, chunk 4 s + l / 16 of step s.
+    const unsigned base = lds_addr(ring);
+    const unsigned swz = (unsigned)((lane >> 4) ^ ((lane >> 1) & 7));
+    const unsigned a_lane = base + (unsigned)((wave * MB * 16 + (lane & 15)) * kWRow);
+    const unsigned b_lane = base + (unsigned)((kTM + (lane & 15)) * kWRow);
+    f32x4 acc[MB][NB];
+    unsigned long long best[NB];
+    #pragma unroll
+    for (int n = 0; n < NB; ++n) {
+        best[n] = 0ull;
+        #pragma unroll
+        for (int m = 0; m < MB; ++m) acc[m][n] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    int k = 0, stage = 0, v0 = vbeg;
+    for (int x = 0; x < total; ++x) {
+        // unit x has landed: S - 2 units of loads may be in flight (fewer at the
+        // end; hidden loads alone once this wave has no weight rows to load)
+        if (x + S - 2 >= total) wait_vmcnt<0>();
+        else if (iw) wait_vmcnt<(S - 2) * (kWL + kHL)>();
+        else wait_vmcnt<(S - 2) * kHL>();
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        if (x + S - 1 < total) issue();                  // into the stage that held unit x - 1
+        if (wave * MB * 16 < vend - v0) {
+            u32x4 fa[2][MB], fb[2][NB];
+            auto reads = [&](int s) {
+                const unsigned off = (unsigned)stage * kStage + ((swz ^ (unsigned)(4 * s)) << 4);
+                #pragma unroll
+                for (int m = 0; m < MB; ++m)
+                    asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(fa[s][m]) : "v"(a_lane + off), "i"(m * 16 * kWRow));
+                #pragma unroll
+                for (int n = 0; n < NB; ++n)
+                    asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(fb[s][n]) : "v"(b_lane + off), "i"(n * 16 * kWRow));
+            };
+            reads(0);
+            #pragma unroll
+            for (int s = 0; s < 2; ++s) {
+                if (s == 0) {
+                    reads(1);
+                    asm volatile("s_waitcnt lgkmcnt(%0)" ::"n"(MB + NB) : "memory");
+                } else {
+                    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+                }
+                #pragma unroll
+                for (int m = 0; m < MB; ++m) tie(fa[s][m]);
+                #pragma unroll
+                for (int n = 0; n < NB; ++n) tie(fb[s][n]);
+                #pragma unroll
+                for (int n = 0; n < NB; ++n)
+                    #pragma unroll
+                    for (int m = 0; m < MB; ++m)
+                        acc[m][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                            __builtin_bit_cast(bf16x8, fa[s][m]), __builtin_bit_cast(bf16x8, fb[s][n]),
+                            acc[m][n], 0, 0, 0);
+            }
+        }
+        stage = stage == S - 1 ? 0 : stage + 1;
+        if (++k == U) {
+            // acc[m][n][e] of lane l: hidden row 16 n + l % 16, vocabulary
+            // entry 16 m + 4 (l / 16) + e of the wave's rows
+            const int vb = v0 + wave * MB * 16 + 4 * (lane >> 4);
+            #pragma unroll
+            for (int n = 0; n < NB; ++n)
+                #pragma unroll
+                for (int m = 0; m < MB; ++m) {
+                    #pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const int v = vb + 16 * m + e;
+                        const unsigned long long key = pack_key(order_key(acc[m][n][e]), (unsigned)v);
+                        best[n] = v < vend ? umax64(best[n], key) : best[n];
+                    }
+                    acc[m][n] = f32x4{0.f, 0.f, 0.f, 0.f};
+                }
+            k = 0;
+            v0 += kTM;
+        }
+    }
+    // lanes l, l ^ 16, l ^ 32, l ^ 48 hold the same hidden row; then the waves
+    // meet in LDS (free once every wave is past its last fragment read)
+    unsigned long long *kx = reinterpret_cast<unsigned long long *>(ring);
+    __syncthreads();
+    #pragma unroll
+    for (int n = 0; n < NB; ++n) {
+        const unsigned long long b = halves_max64(rows_max64(best[n]));
+        if (lane < 16) kx[wave * NB * 16 + n * 16 + lane] = b;
+    }
+    __syncthreads();
+    if (tid < NB * 16 && tid < R) {
+        unsigned long long b = kx[tid];
+        #pragma unroll
+        for (int u = 1; u < WV; ++u) b = umax64(b, kx[u * NB * 16 + tid]);
+        atomicMax(keys + tid, b);
+    }
+}
+
+}  // namespace
+
+namespace {
+
+template <int NB, int MB, int S, int WV>
+hipError_t launch_stream(int groups, const uint16_t *hidden, const uint16_t *w, int R, int V, int d,
+                         unsigned long long *keys, hipStream_t s) {
+    const int most = (V + 15) / 16;                  // no range shorter than one wave's 16 rows
+    return launch_kernel(lm_head_stream_kernel<NB, MB, S, WV>, dim3(groups < most ? groups : most),
+                         dim3(WV * kWave), s, hidden, w, R, V, d, keys);
+}
+
+// Which split of the vocabulary the weight stream takes, by the rows a CU gets
+// (V / 256). us at d = 4096 unless stated, 64 rows or 24 rows:
+//   * V >= 98304 (384 rows per CU, at least 1.5 tiles of 256): one workgroup of
+//     8 waves x 32 rows per CU; the taller tile re-reads the hidden rows half as
+//     often (V = 128256: 155 against 179 with 16 rows per wave, 204 with two
+//     workgroups per CU; V = 75000, d = 2048: 77 against 71 with the next one).
+//   * 40960 <= V: two workgroups of 8 waves x 16 rows per CU (V = 50257: 77
+//     against 87-89 with one workgroup per CU).
+//   * 24576 <= V and d >= 2048: two workgroups of 4 waves x 16 rows per CU, a
+//     range of at most 80 rows each (V = 32000, 24 rows: 47 against 55-57).
+//   * below, or with a short K loop, starting 512 workgroups costs more than
+//     their overlap gains: one workgroup of 8 waves x 16 rows per CU (V = 12000,
+//     d = 1024: 11 against 15; V = 32000, d = 1024: 15 against 18).
+// More than 64 rows: the hidden units fill the ring, one workgroup per CU; 32
+// rows per wave halve its LDS reads of them (V = 128256: 173 against 202-211).
+hipError_t launch_stream_rows(const uint16_t *hidden, const uint16_t *w, int R, int V, int d,
+                              unsigned long long *keys, hipStream_t s) {
+    if (R > 64) return launch_stream<8, 2, 3, 8>(256, hidden, w, R, V, d, keys, s);
+    if (V >= 98304)
+        return R > 32 ? launch_stream<4, 2, 4, 8>(256, hidden, w, R, V, d, keys, s)
+                      : launch_stream<2, 2, 4, 8>(256, hidden, w, R, V, d, keys, s);
+    if (V >= 24576 && V < 40960 && d >= 2048)
+        return R > 32 ? launch_stream<4, 1, 4, 4>(512, hidden, w, R, V, d, keys, s)
+                      : launch_stream<2, 1, 6, 4>(512, hidden, w, R, V, d, keys, s);
+    const int groups = V >= 40960 ? 512 : 256;
+    return R > 32 ? launch_stream<4, 1, 3, 8>(groups, hidden, w, R, V, d, keys, s)
+                  : launch_stream<2, 1, 3, 8>(groups, hidden, w, R, V, d, keys, s);
+}
+
 }  // namespace
 
 int lm_head_vocab_tiles(int V) { return (int)(((long long)V + kTileM - 1) / kTileM); }
@@ -391,6 +634,12 @@ hipError_t launch_lm_head_argmax_accept(const uint16_t *hidden, const uint16_t *
     const int R = B * N;
     hipError_t e = launch_kernel(lm_keys_clear_kernel, dim3((R + 255) / 256), dim3(256), s, keys, R);
     if (e != hipSuccess) return e;
+    if (R <= kStreamRows) {
+        e = launch_stream_rows(hidden, w, R, V, d, keys, s);
+        if (e != hipSuccess) return e;
+        return launch_accept(keys, 1, draft, parent, num_nodes, B, N, argmax_out, accept_len,
+                             accept_idx, bonus, s);
+    }
     const int vtiles = lm_head_vocab_tiles(V);
     const int rblocks = (R + kTileN - 1) / kTileN;
     const int groups = (vtiles + kNumXcd - 1) / kNumXcd * kNumXcd * rblocks;

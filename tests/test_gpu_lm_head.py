@@ -102,6 +102,35 @@ def test_lm_head_cases(oracle_mod, case):
     check_accept(oracle_mod, x, got, f"lm{case}")
 
 
+FEW_ROWS = [
+    # (B, N, V, d): every split of the weight stream (up to 128 rows) at its edges
+    (1, 1, 5, 64),             # one row, one unit, a vocabulary shorter than a wave's rows
+    (1, 16, 257, 128),         # ranges of 15 and 16 rows
+    (1, 17, 1000, 192),
+    (1, 24, 24600, 2048),      # two 4-wave workgroups per CU: up to 32 rows,
+    (1, 33, 24577, 2048),      # up to 64
+    (1, 32, 40961, 128),       # two 8-wave workgroups per CU: up to 32 rows,
+    (2, 20, 41000, 64),        # up to 64; a range's second tile has idle waves
+    (3, 8, 99999, 128),        # 32 rows per wave, up to 32 rows,
+    (1, 64, 98305, 64),        # up to 64
+    (1, 65, 3000, 320),        # more than 64 rows: the smallest and the largest
+    (2, 64, 98400, 64),
+    (3, 43, 2000, 128),        # 129 rows: the tiled product
+]
+
+
+@pytest.mark.parametrize("case", range(len(FEW_ROWS)))
+def test_lm_head_few_rows(oracle_mod, case):
+    """The same bound as the other cases (any fp32 summation order)."""
+    T = U.require_gpu()
+    B, N, V, d = FEW_ROWS[case]
+    print(f"case lm few rows {case}: B={B} N={N} V={V} d={d}", flush=True)
+    x = W.make_lm_head_inputs(f"few{case}", 330 + case, B=B, N=N, V=V, d=d)
+    got = run_gpu(T, x)
+    check_argmax(oracle_mod, x, got[0], real_rows(x), f"few{case}")
+    check_accept(oracle_mod, x, got, f"few{case}")
+
+
 def test_lm_head_full_size_row_block(oracle_mod):
     """The 8B-shaped head (vocabulary 128256, hidden size 4096, 16 x 64 nodes)
     in the launch configuration the benchmark times; the oracle checks one
