@@ -15,34 +15,37 @@
 // (lm_head_stream_kernel, described there); more rows take a tiled matrix
 // product (lm_head_argmax_kernel):
 //
-//   * Workgroup tile: 256 vocabulary entries (MFMA M) x 256 hidden rows
-//     (MFMA N), the largest whose fp32 accumulators fit a CU's registers.
-//     Eight waves (two per SIMD, so one wave's waits are covered by the
-//     other's matrix work) in a 2 x 4 arrangement, each accumulating a
-//     128 x 64 block in 8 v_mfma_f32_32x32x16_bf16 accumulators.
+//   * Tile: 256 vocabulary entries (MFMA M) x 256 hidden rows (MFMA N), the
+//     largest whose fp32 accumulators fit a CU's registers. Four waves, one per
+//     SIMD, in a 2 x 2 arrangement, each accumulating a 128 x 128 block in 16
+//     v_mfma_f32_32x32x16_bf16 accumulators (256 registers): a wave's LDS reads
+//     per MFMA are a third less than with eight waves of 128 x 64, whose reads
+//     and incoming lines together need the LDS for as long as the products need
+//     the matrix cores.
 //   * Both operands are K-contiguous (W is [V, d], hidden is [R, d]) and both
-//     stream into LDS through global_load_lds_dwordx4, each in its own ring.
-//     The weight, which comes from HBM and whose load latency bounds the
-//     stream, moves in 64-deep units (each row's 128 bytes = whole cache
-//     lines; a 1 KB load covers 8 rows) through a 3-stage ring, two units in
-//     flight; the hidden rows, re-read from L2, move in 32-deep slices (16
-//     rows x 64 bytes per load) through a 4-stage ring, issued 1.5 units ahead.
-//     Together 160 KB: the whole LDS. The 16-byte chunks of each row are
-//     XOR-swizzled by the row index so the operand reads (16 rows at one chunk
-//     per LDS pass) are free of bank conflicts.
-//   * Each 16-deep K step's 8 MFMAs carry, one by one, the next step's 6
-//     fragment reads; two ring hand-offs per unit (s_waitcnt vmcnt +
-//     s_barrier), a few MFMAs into steps 1 and 3 after this wave's last read of
-//     the stages refilled next, are followed by the refill loads.
+//     stream into LDS through global_load_lds_dwordx4 in 64-deep units (each
+//     row's 128 bytes = whole cache lines; a 1 KB load covers 8 rows): the
+//     weight, whose load latency bounds the stream, through a 3-stage ring, the
+//     hidden rows, re-read from L2, through a 2-stage ring. Together 160 KB: the
+//     whole LDS. The 16-byte chunks of each row are XOR-swizzled by the row
+//     index so the operand reads are free of bank conflicts.
+//   * One barrier per unit. Each 16-deep K step's 16 MFMAs carry the next step's
+//     8 fragment reads and a quarter of the unit's loads.
+//   * One workgroup per CU walks its tiles without draining the rings between
+//     them; its best keys stay in registers while its row block stays the same.
 //   * The four row blocks of one vocabulary tile run together on one XCD and
 //     share its L2 copy of the weight tile; each takes the units of every
 //     aligned group of four in an order rotated by its row block, so the four
 //     ask HBM for different lines at any time (more distinct bytes in flight)
 //     and find the others' lines in L2 a few units later.
-//   * Epilogue: each lane folds its 64 values per row into a key, lanes l and
-//     l ^ 32 combine, the two waves of a row block combine through LDS, and a
-//     64-bit atomic maximum per (row, vocabulary tile) merges the tiles into
-//     the row's key, which the greedy acceptance kernel then decodes.
+//   * A tile's values become keys by a maximum and then a search for its lowest
+//     entry (fold below); lanes l and l ^ 32 combine, and a 64-bit atomic
+//     maximum per row merges waves and workgroups into the row's key, which the
+//     greedy acceptance kernel then decodes.
+// Measured at 1024 rows x 128256 x 4096: 835 us (1290 TFLOP/s, matrix pipe busy
+// 75 % of the cycles) against 898-915 us (66 %) for eight waves, one tile per
+// workgroup and a 64-bit compare per value. Of the rest, about 130 us is the
+// issue of the loads: without them the same loop takes 707 us.
 #include "tv_internal.h"
 
 namespace tv {
@@ -53,7 +56,7 @@ namespace {
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int kWaves = 8;                              // two per SIMD
+constexpr int kWaves = 4;                              // one per SIMD
 constexpr int kLmThreads = kWaves * kWave;
 constexpr int kTileM = 256;                            // vocabulary entries per workgroup
 constexpr int kTileN = 256;                            // hidden rows per workgroup
@@ -61,24 +64,19 @@ constexpr int kUnitK = 64;                             // K depth of one weight 
 constexpr int kWRow = kUnitK * 2;                      // bytes of one weight row's unit (128)
 constexpr int kWUnitBytes = kTileM * kWRow;            // 32 KB
 constexpr int kWStages = 3;
-constexpr int kHK = 32;                                // K depth of one hidden slice
-constexpr int kHRow = kHK * 2;                         // bytes of one hidden row's slice (64)
-constexpr int kHSliceBytes = kTileN * kHRow;           // 16 KB
-constexpr int kHStages = 4;
-constexpr int kWLoads = kWUnitBytes / (kLmThreads * 16);    // 1 KB loads per thread per unit (4)
-constexpr int kHLoads = kHSliceBytes / (kLmThreads * 16);   // per slice (2)
-constexpr int kWaveM = 128;                            // per-wave block: 2 waves along M
-constexpr int kWaveN = kTileN / (kWaves / 2);
+constexpr int kHStages = 2;
+constexpr int kLoads = kWUnitBytes / (kLmThreads * 16);     // 1 KB loads per wave and unit, each operand
+constexpr int kWaveM = 128, kWaveN = 128;              // per-wave block: 2 x 2 waves
 constexpr int kFragM = kWaveM / 32, kFragN = kWaveN / 32;
 constexpr int kReads = kFragM + kFragN;                // fragment reads per K step
 constexpr int kSteps = kFragM * kFragN;                // MFMAs per K step
-constexpr int kPre = 2;                                // MFMAs before a hand-off
+constexpr int kPre = 2;                                // MFMAs before the hand-off
 constexpr int kStreamRows = 128;                       // most rows of lm_head_stream_kernel
-static_assert(kWLoads * kWaves * 8 == kTileM && kHLoads * kWaves * 16 == kTileN, "load blocks");
-static_assert(kWStages * kWUnitBytes + kHStages * kHSliceBytes <= 160 * 1024, "LDS");
+static_assert(kLoads * kWaves * 8 == kTileM && kTileM == kTileN && kFragM == kFragN, "load blocks");
+static_assert((kWStages + kHStages) * kWUnitBytes <= 160 * 1024, "LDS");
 
 __shared__ __attribute__((aligned(1024))) unsigned char g_lm_w[kWStages * kWUnitBytes];
-__shared__ __attribute__((aligned(1024))) unsigned char g_lm_h[kHStages * kHSliceBytes];
+__shared__ __attribute__((aligned(1024))) unsigned char g_lm_h[kHStages * kWUnitBytes];
 
 __device__ __forceinline__ unsigned lds_addr(const void *p) {
     return (unsigned)(size_t)(const LDS_AS void *)p;
@@ -98,15 +96,15 @@ __device__ __forceinline__ void wait_vmcnt() {
     __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
 }
 
-__device__ __forceinline__ void wait_vmcnt_rt(int n) {     // n in {0, 2, 4, 8}
-    if (n >= 8) wait_vmcnt<8>();
-    else if (n >= 4) wait_vmcnt<4>();
-    else if (n >= 2) wait_vmcnt<2>();
-    else wait_vmcnt<0>();
-}
-
 __device__ __forceinline__ unsigned long long umax64(unsigned long long a, unsigned long long b) {
     return a > b ? a : b;
+}
+
+// Maximum of three values, NaN if any is NaN.
+__device__ __forceinline__ float maximum3(float a, float b, float c) {
+    float r;
+    asm("v_maximum3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+    return r;
 }
 
 // Maximum of a 64-bit key held by lanes l and l ^ 32.
@@ -134,88 +132,118 @@ __global__ void lm_keys_clear_kernel(unsigned long long *__restrict__ keys, int 
     if (i < R) keys[i] = 0ull;                  // below every real key
 }
 
-// grid: kNumXcd * ceil(vtiles / kNumXcd) * rblocks workgroups of kLmThreads threads.
-// d is a multiple of kUnitK.
+// Workgroups: any number; `groups` = kNumXcd * ceil(vtiles / kNumXcd) * rblocks
+// tiles. d is a multiple of kUnitK.
 __global__ __launch_bounds__(kLmThreads, 1) void lm_head_argmax_kernel(
     const uint16_t *__restrict__ hidden, const uint16_t *__restrict__ w, int R, int V, int d,
-    int vtiles, int rblocks, unsigned long long *__restrict__ keys) {
-    const int id = blockIdx.x;
-    const int local = id / kNumXcd;
-    const int vt = (local / rblocks) * kNumXcd + id % kNumXcd;
-    const int rb = local % rblocks;
-    if (vt >= vtiles) return;                    // whole workgroup, before any barrier
-    const int v0 = vt * kTileM, r0 = rb * kTileN;
+    int vtiles, int rblocks, int groups, unsigned long long *__restrict__ keys) {
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int lane = tid & (kWave - 1);
-    const int U = d / kUnitK;                    // weight units; hidden slices: 2 U
+    const int U = d / kUnitK;
+    const int step_id = gridDim.x;
+    // Tile `id`: vocabulary tile and row block. Ids past the last vocabulary
+    // tile (the last group of eight) are empty and skipped.
+    auto vt_of = [&](int id) { return (id / kNumXcd / rblocks) * kNumXcd + id % kNumXcd; };
+    auto rb_of = [&](int id) { return (id / kNumXcd) % rblocks; };
+    auto next_id = [&](int id) {
+        do id += step_id; while (id < groups && vt_of(id) >= vtiles);
+        return id;
+    };
+    const int first = next_id((int)blockIdx.x - step_id);
+    if (first >= groups) return;                 // whole workgroup, before any barrier
+    int total = 0;                               // units of this workgroup
+    for (int id = first; id < groups; id = next_id(id)) total += U;
 
-    // Weight loads: instruction i of wave w fills 1 KB block (4w + i) of a
-    // unit = rows 8 (4w + i) .. +7; lane p writes row p / 8, position p % 8,
-    // which holds chunk (p % 8) ^ ((row >> 1) & 7). Hidden loads: instruction
-    // i fills block (2w + i) of a slice = rows 16 (2w + i) .. +15; lane p
-    // writes row p / 4, position p % 4 = chunk (p % 4) ^ ((row >> 2) & 3).
-    // Rows past the end of W or hidden read the last row (finite data; the
-    // results are discarded).
-    const char *wsrc[kWLoads], *hsrc[kHLoads];
-    {
-        #pragma unroll
-        for (int i = 0; i < kWLoads; ++i) {
-            const int row = (wave * kWLoads + i) * 8 + (lane >> 3);
-            const int chunk = (lane & 7) ^ ((row >> 1) & 7);
-            wsrc[i] = reinterpret_cast<const char *>(w + (size_t)min(v0 + row, V - 1) * d) + chunk * 16;
-        }
-        #pragma unroll
-        for (int i = 0; i < kHLoads; ++i) {
-            const int row = (wave * kHLoads + i) * 16 + (lane >> 2);
-            const int chunk = (lane & 3) ^ ((row >> 2) & 3);
-            hsrc[i] = reinterpret_cast<const char *>(hidden + (size_t)min(r0 + row, R - 1) * d) + chunk * 16;
-        }
-    }
+    // Loads: instruction i of wave w fills 1 KB block (8w + i) of a weight or
+    // hidden unit = rows 8 (8w + i) .. +7; lane p writes row p / 8, position
+    // p % 8, which holds chunk (p % 8) ^ ((row >> 1) & 7). Rows past the end of
+    // W or hidden read the last row (finite data; the results are discarded).
+    // A cursor is an operand's unit to load next: wave-uniform state only (the
+    // lane's offset is computed behind each MFMA that a load follows; d < 2^23,
+    // so it fits 32 bits and the factors 24).
+    int lrow = wave * kLoads * 8 + (lane >> 3);
+    unsigned lchunk0 = (unsigned)(((lane & 7) ^ ((lane >> 4) & 3)) << 4);   // rows 8 (8w + i) + .., i even
+    const unsigned rowb = (unsigned)d * 2;
     // Unit order: inside every complete aligned group of four, rotated by the
     // row block (a permutation of 0 .. U - 1).
     const int U4 = U & ~3;
-    auto unit_of = [&](int u) { return u < U4 ? (u & ~3) | ((u + rb) & 3) : u; };
-    // Load i of a weight unit / hidden slice: LDS stage offset, K byte offset.
-    auto issue_w = [&](unsigned stage_off, size_t koff, int i) {
-        __builtin_amdgcn_global_load_lds((const GLOBAL_AS void *)(wsrc[i] + koff),
-                                         (LDS_AS void *)(g_lm_w + stage_off + (wave * kWLoads + i) * 1024),
-                                         16, 0, 0);
+    struct Cursor {
+        const char *base, *at;                           // the tile's first row; the unit in it
+        int last;                                        // the tile's last existing row
+        int id, u, rb;
+        unsigned stage;                                  // LDS byte offset
+    } cw, ch;
+    auto set_unit = [&](Cursor &c) {
+        c.at = c.base + (size_t)(c.u < U4 ? (c.u & ~3) | ((c.u + c.rb) & 3) : c.u) * kWRow;
     };
-    auto issue_h = [&](unsigned stage_off, size_t koff, int i) {
-        __builtin_amdgcn_global_load_lds((const GLOBAL_AS void *)(hsrc[i] + koff),
-                                         (LDS_AS void *)(g_lm_h + stage_off + (wave * kHLoads + i) * 1024),
-                                         16, 0, 0);
+    auto set_tile = [&](Cursor &c, const uint16_t *p, int r0, int rows) {
+        c.rb = rb_of(c.id);
+        c.base = reinterpret_cast<const char *>(p) + (size_t)r0 * rowb;
+        c.last = rows - 1 - r0;
     };
+    auto set_w = [&]() { set_tile(cw, w, vt_of(cw.id) * kTileM, V); };
+    auto set_h = [&]() { set_tile(ch, hidden, rb_of(ch.id) * kTileN, R); };
+    auto issue = [&](const Cursor &c, unsigned char *ring, int i) {
+        const unsigned row = (unsigned)min(lrow + 8 * i, c.last);
+        const unsigned off = __umul24(row, rowb) + (lchunk0 ^ (unsigned)((i & 1) << 6));
+        __builtin_amdgcn_global_load_lds((const GLOBAL_AS void *)(c.at + off),
+                                         (LDS_AS void *)(ring + c.stage + (wave * kLoads + i) * 1024), 16, 0, 0);
+    };
+    auto issue_w = [&](int i) { issue(cw, g_lm_w, i); };
+    auto issue_h = [&](int i) { issue(ch, g_lm_h, i); };
+    auto advance_w = [&]() {
+        cw.stage = cw.stage == (kWStages - 1) * kWUnitBytes ? 0 : cw.stage + kWUnitBytes;
+        if (++cw.u == U) {
+            cw.u = 0;
+            cw.id = next_id(cw.id);
+            if (cw.id < groups) set_w();
+        }
+        set_unit(cw);
+    };
+    auto advance_h = [&]() {
+        ch.stage ^= kWUnitBytes;
+        if (++ch.u == U) {
+            ch.u = 0;
+            ch.id = next_id(ch.id);
+            if (ch.id < groups) set_h();
+        }
+        set_unit(ch);
+    };
+    cw.id = ch.id = first;
+    cw.u = ch.u = 0;
+    cw.stage = ch.stage = 0;
+    set_w();
+    set_h();
+    set_unit(cw);
+    set_unit(ch);
 
     // Operand fragments of v_mfma_f32_32x32x16_bf16: lane l reads row l % 32
     // of a 32-row block, K elements 8 (l / 32) .. +7 of the 16-deep step.
-    // Step s (0..3) of a unit is weight chunk 2 s + l / 32, whose position is
-    // (l / 32) ^ ((row >> 1) & 7) ^ 2 s, and hidden slice s / 2, chunk
-    // 2 (s % 2) + l / 32 at position (l / 32) ^ ((row >> 2) & 3) ^ 2 (s % 2).
+    // Step s (0..3) of a unit is chunk 2 s + l / 32, at position
+    // (l / 32) ^ ((row >> 1) & 7) ^ 2 s.
     const int wm = wave & 1, wn = wave >> 1;
-    const unsigned wring = lds_addr(g_lm_w), hring = lds_addr(g_lm_h);
-    const unsigned a_lane = wring + (unsigned)((wm * kWaveM + (lane & 31)) * kWRow) +
-                            (unsigned)((((lane >> 5) ^ (lane >> 1)) & 7) << 4);
-    const unsigned b_lane = hring + (unsigned)((wn * kWaveN + (lane & 31)) * kHRow) +
-                            (unsigned)((((lane >> 5) ^ (lane >> 2)) & 3) << 4);
+    const unsigned swz = (unsigned)((((lane >> 5) ^ (lane >> 1)) & 7) << 4);
+    const unsigned a_lane = lds_addr(g_lm_w) + (unsigned)((wm * kWaveM + (lane & 31)) * kWRow) + swz;
+    const unsigned b_lane = lds_addr(g_lm_h) + (unsigned)((wn * kWaveN + (lane & 31)) * kWRow) + swz;
 
     f32x16 acc[kFragM][kFragN];
-    #pragma unroll
-    for (int m = 0; m < kFragM; ++m)
-        #pragma unroll
-        for (int n = 0; n < kFragN; ++n)
-            #pragma unroll
-            for (int e = 0; e < 16; ++e) acc[m][n][e] = 0.f;
     u32x4 fa[2][kFragM], fb[2][kFragN];
-
-    // Read q (0..5) of a fragment set: A fragments 0..3, then B fragments 0..1.
+    auto clear = [&]() {
+        #pragma unroll
+        for (int m = 0; m < kFragM; ++m)
+            #pragma unroll
+            for (int n = 0; n < kFragN; ++n)
+                #pragma unroll
+                for (int e = 0; e < 16; ++e) acc[m][n][e] = 0.f;
+    };
+    clear();
+    // Read q (0..7) of a fragment set, in the order the products use them.
     auto read_q = [&](int set, unsigned aa, unsigned ba, int q) {
-        if (q < kFragM)
-            asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(fa[set][q]) : "v"(aa), "i"(q * 32 * kWRow));
+        if (q & 1)
+            asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(fb[set][q >> 1]) : "v"(ba), "i"((q >> 1) * 32 * kWRow));
         else
-            asm volatile("ds_read_b128 %0, %1 offset:%2"
-                         : "=v"(fb[set][q - kFragM]) : "v"(ba), "i"((q - kFragM) * 32 * kHRow));
+            asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(fa[set][q >> 1]) : "v"(aa), "i"((q >> 1) * 32 * kWRow));
     };
     auto ready = [&](int set) {             // after lds_wait_all: the set is in registers
         #pragma unroll
@@ -230,165 +258,149 @@ __global__ __launch_bounds__(kLmThreads, 1) void lm_head_argmax_kernel(
             acc[m][n], 0, 0, 0);
     };
 
-    // Issue order, the same in the prologue and the steady state: hand-off A
-    // of unit u (in step 1) issues hidden slice 2u + 4; hand-off B (in step 3)
-    // issues weight unit u + 3, then hidden slice 2u + 5. Stages: weight unit
-    // x in x % 3, hidden slice x in x % 4. The prologue plays hand-offs
-    // B(-3), A(-2), B(-2), A(-1), B(-1).
-    {
-        const size_t k0 = (size_t)unit_of(0) * kWRow, k1 = (size_t)unit_of(1) * kWRow;
+    // Best key of hidden row 32 n + l % 32 of the wave's block so far.
+    unsigned long long best[kFragN];
+    #pragma unroll
+    for (int n = 0; n < kFragN; ++n) best[n] = 0ull;
+    // acc[m][n][e] of lane l: hidden row 32 n + l % 32 of the wave's block,
+    // vocabulary entry 32 m + 8 (e / 4) + 4 (l / 32) + e % 4. The largest value
+    // first (NaN propagating), then the lowest entry that has it: for a finite
+    // nonzero maximum t, x - t has the sign bit unless x == t, so the minimum of
+    // bits(x - t) | entry over the lane's values is that entry. Rows past the
+    // end of W were loaded as its last row, and stand for it.
+    auto fold = [&](int vt) {
+        const int vbase = vt * kTileM + wm * kWaveM + 4 * (lane >> 5);
         #pragma unroll
-        for (int i = 0; i < kWLoads; ++i) issue_w(0, k0, i);                          // W0
-        #pragma unroll
-        for (int i = 0; i < kHLoads; ++i) issue_h(0, k0, i);                          // H0
-        if (U >= 2)
+        for (int n = 0; n < kFragN; ++n) {
+            float t = acc[0][n][0];
             #pragma unroll
-            for (int i = 0; i < kWLoads; ++i) issue_w(kWUnitBytes, k1, i);            // W1
-        #pragma unroll
-        for (int i = 0; i < kHLoads; ++i) issue_h(kHSliceBytes, k0 + kHRow, i);       // H1
-        if (U >= 2)
-            #pragma unroll
-            for (int i = 0; i < kHLoads; ++i) issue_h(2 * kHSliceBytes, k1, i);       // H2
-        if (U >= 3) {
-            const size_t k2 = (size_t)unit_of(2) * kWRow;
-            #pragma unroll
-            for (int i = 0; i < kWLoads; ++i) issue_w(2 * kWUnitBytes, k2, i);        // W2
+            for (int q = 1; q + 1 < kFragM * 16; q += 2)
+                t = maximum3(t, acc[q >> 4][n][q & 15], acc[(q + 1) >> 4][n][(q + 1) & 15]);
+            t = maximum3(t, acc[kFragM - 1][n][15], acc[kFragM - 1][n][15]);
+            unsigned at = 0xFFu;
+            if (__any(!(fabsf(t) < __builtin_huge_valf()) || t == 0.f)) {   // -0 == +0
+                const bool tn = t != t;
+                #pragma unroll
+                for (int q = kFragM * 16 - 1; q >= 0; --q) {
+                    const float x = acc[q >> 4][n][q & 15];
+                    if (x == t || (tn && x != x)) at = (unsigned)q;
+                    tie(at);
+                }
+            } else {
+                #pragma unroll
+                for (int q = 0; q < kFragM * 16; q += 2)
+                    at = min(at, min(__float_as_uint(acc[q >> 4][n][q & 15] - t) | (unsigned)q,
+                                     __float_as_uint(acc[q >> 4][n][(q & 15) + 1] - t) | (unsigned)(q + 1)));
+            }
+            const int v = min(vbase + (int)(32 * (at >> 4) + 8 * ((at >> 2) & 3) + (at & 3)), V - 1);
+            best[n] = umax64(best[n], pack_key(order_key(t), (unsigned)v));
         }
-        if (U >= 2)
-            #pragma unroll
-            for (int i = 0; i < kHLoads; ++i) issue_h(3 * kHSliceBytes, k1 + kHRow, i);   // H3
-        // Unit 0 needs W0 and H0; what came after may stay in flight.
-        if (U >= 3) wait_vmcnt<kHLoads + kWLoads + 2 * kHLoads + kWLoads>();
-        else if (U >= 2) wait_vmcnt<kHLoads + kWLoads + 2 * kHLoads>();
-        else wait_vmcnt<kHLoads>();
+        clear();
+    };
+    // One atomic maximum per row and M-wave once the row block is done.
+    auto flush = [&](int rb) {
+        #pragma unroll
+        for (int n = 0; n < kFragN; ++n) {
+            const unsigned long long b = halves_max64(best[n]);
+            const int row = rb * kTileN + wn * kWaveN + 32 * n + lane;
+            if (lane < 32 && row < R) atomicMax(keys + row, b);
+            best[n] = 0ull;
+        }
+    };
+
+    // W0, H0, W1 and half of H1 up front; unit 0 needs the first 2 kLoads.
+    constexpr int kHalf = kLoads / 2;
+    #pragma unroll
+    for (int i = 0; i < kLoads; ++i) issue_w(i);
+    #pragma unroll
+    for (int i = 0; i < kLoads; ++i) issue_h(i);
+    advance_w();
+    advance_h();
+    if (total > 1) {
+        #pragma unroll
+        for (int i = 0; i < kLoads; ++i) issue_w(i);
+        #pragma unroll
+        for (int i = 0; i < kHalf; ++i) issue_h(i);
+        advance_w();
+        wait_vmcnt<kLoads + kHalf>();
+    } else {
+        wait_vmcnt<0>();
     }
     __builtin_amdgcn_s_barrier();
     #pragma unroll
     for (int q = 0; q < kReads; ++q) read_q(0, a_lane, b_lane, q);
+    lds_wait_all();
+    ready(0);
 
-    // One unit u (4 steps of 16). Step s's fragments are in set s & 1. Steps 0
-    // and 2: 8 MFMAs with the next step's 6 reads between them. Steps 1 and 3:
-    // kPre MFMAs, the hand-off (the data of the next reads landed everywhere;
-    // every wave is done with the stages refilled now), then the remaining
-    // MFMAs carrying the hand-off's loads and then the next step's reads.
-    // sched_barrier pins the interleaving. kSteady: u + 3 < U, so every load
-    // of the hand-offs exists and the waits are constant.
-    int wst = 0;                                      // weight stage of unit u
-    auto unit = [&](int u, auto steady_c) {
+    // One unit x: 4 steps of 16 MFMAs, step s's fragments in set s & 1, the
+    // next step's reads behind the first MFMAs, one load behind every fourth
+    // MFMA. In step 3 every fragment of unit x is in registers: the hand-off
+    // (unit x + 1 has landed everywhere; every wave is done with unit x) is
+    // followed by the reads of unit x + 1 and the first half of the hidden unit
+    // x + 2 (into the stage of unit x), whose second half follows in the next
+    // unit's step 0; steps 1 and 2 load the weight of unit x + 2 (into the stage
+    // of unit x - 1). sched_barrier pins the interleaving. kSteady: x + 2 < total, so every load exists and the waits are constant.
+    int wst = 0;
+    unsigned hst = 0;
+    auto unit = [&](int x, auto steady_c) {
         constexpr bool kSteady = decltype(steady_c)::value;
-        const unsigned wcur = (unsigned)wst * kWUnitBytes;
-        const unsigned wnxt = (unsigned)(wst == kWStages - 1 ? 0 : wst + 1) * kWUnitBytes;
-        const unsigned hcur = (unsigned)(u & 1) * 2 * kHSliceBytes;     // stage of slice 2u
-        const unsigned a0 = a_lane + wcur, a1 = a_lane + wnxt;
-        const unsigned b0 = b_lane + hcur, b1 = b_lane + (hcur ^ 2 * kHSliceBytes);
-        const size_t kw = (size_t)unit_of(u + 3) * kWRow;              // weight unit u + 3
-        const size_t kh = (size_t)unit_of(u + 2) * kWRow;              // hidden slices 2u + 4, 2u + 5
-        const bool has_w = kSteady || u + 3 < U;
-        const bool has_h = kSteady || u + 2 < U;
-        const bool has_next = kSteady || u + 1 < U;
-
+        const int wnx = wst == kWStages - 1 ? 0 : wst + 1;
+        const unsigned a0 = a_lane + (unsigned)wst * kWUnitBytes, a1 = a_lane + (unsigned)wnx * kWUnitBytes;
+        const unsigned b0 = b_lane + hst, b1 = b_lane + (hst ^ kWUnitBytes);
+        const bool next = kSteady || x + 1 < total;
+        tie(lrow);                                       // keep the lane offsets out of registers
+        tie(lchunk0);
         auto step = [&](auto sc) {
             constexpr int s = decltype(sc)::value;
             constexpr int set = s & 1;
             const unsigned aa = s == 3 ? a1 : a0 ^ ((unsigned)(s + 1) << 5);
-            const unsigned ba = s == 3 ? b1
-                                       : (b0 + (unsigned)(((s + 1) >> 1) * kHSliceBytes)) ^
-                                             ((unsigned)((s + 1) & 1) << 5);
+            const unsigned ba = s == 3 ? b1 : b0 ^ ((unsigned)(s + 1) << 5);
             lds_wait_all();
             ready(set);
-            if constexpr (s == 0 || s == 2) {
-                #pragma unroll
-                for (int q = 0; q < kSteps; ++q) {
-                    mfma_q(set, q);
+            #pragma unroll
+            for (int q = 0; q < kSteps; ++q) {
+                mfma_q(set, q);
+                if (s == 3) {
+                    if (q == kPre - 1 && next) {
+                        if (kSteady) wait_vmcnt<kLoads>();        // W(x + 2) may be in flight
+                        else wait_vmcnt<0>();
+                        __builtin_amdgcn_s_barrier();
+                    }
+                    if (q >= kPre && q < kPre + kReads && next) read_q(set ^ 1, aa, ba, q - kPre);
+                } else {
                     if (q < kReads) read_q(set ^ 1, aa, ba, q);
-                    __builtin_amdgcn_sched_barrier(0);
                 }
-            } else {
-                constexpr int kLoadsHere = s == 1 ? kHLoads : kWLoads + kHLoads;
-                constexpr int kOps = kLoadsHere + kReads;
-                constexpr int kPer = (kOps + kSteps - kPre - 1) / (kSteps - kPre);
-                const bool next = s == 1 || has_next;
-                #pragma unroll
-                for (int q = 0; q < kPre; ++q) {
-                    mfma_q(set, q);
-                    __builtin_amdgcn_sched_barrier(0);
+                // step 3: behind the hand-off's reads, else every second MFMA
+                constexpr int kLoad0 = s == 3 ? kPre + kReads + 1 : kReads, kEvery = s == 3 ? 1 : 2;
+                if (q >= kLoad0 && (q - kLoad0) % kEvery == 0 && (q - kLoad0) / kEvery < kHalf) {
+                    const int i = (q - kLoad0) / kEvery;
+                    if (s == 0) { if (next) issue_h(kHalf + i); }
+                    else if (s == 3) { if (kSteady) issue_h(i); }
+                    else if (kSteady) issue_w((s - 1) * kHalf + i);
                 }
-                if (next) {
-                    // loads issued after the newest one the next reads need
-                    if constexpr (kSteady) {
-                        wait_vmcnt<2 * kWLoads>();
-                    } else if constexpr (s == 1) {   // hidden slice 2u + 1 (from B(u - 2))
-                        wait_vmcnt_rt((u + 1 < U ? 4 : 0) + (u + 2 < U ? 4 : 0));
-                    } else {                         // unit u + 1 (B(u - 2)), slice 2u + 2 (A(u - 1))
-                        wait_vmcnt_rt((u + 2 < U ? 6 : 0) + (u + 1 < U ? 2 : 0));
-                    }
-                    __builtin_amdgcn_s_barrier();
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-                #pragma unroll
-                for (int q = kPre; q < kSteps; ++q) {
-                    mfma_q(set, q);
-                    #pragma unroll
-                    for (int x = 0; x < kPer; ++x) {
-                        const int op = (q - kPre) * kPer + x;
-                        if (op < kLoadsHere) {
-                            if (s == 1) {
-                                if (has_h) issue_h(hcur, kh, op);                       // slice 2u + 4
-                            } else if (op < kWLoads) {
-                                if (has_w) issue_w(wcur, kw, op);                       // unit u + 3
-                            } else if (has_h) {
-                                issue_h(hcur + kHSliceBytes, kh + kHRow, op - kWLoads); // slice 2u + 5
-                            }
-                        } else if (op < kOps) {
-                            if (next) read_q(set ^ 1, aa, ba, op - kLoadsHere);
-                        }
-                    }
-                    __builtin_amdgcn_sched_barrier(0);
-                }
+                __builtin_amdgcn_sched_barrier(0);
             }
+            if (s == 0 && next) advance_h();
+            if (s == 2 && kSteady) advance_w();
         };
         step(std::integral_constant<int, 0>());
         step(std::integral_constant<int, 1>());
         step(std::integral_constant<int, 2>());
         step(std::integral_constant<int, 3>());
-        wst = wst == kWStages - 1 ? 0 : wst + 1;
+        wst = wnx;
+        hst ^= kWUnitBytes;
     };
-    int u = 0;
-    for (; u + 3 < U; ++u) unit(u, std::true_type());
-    for (; u < U; ++u) unit(u, std::false_type());
-
-    // Epilogue. acc[m][n][e] of lane l: hidden row 32 n + l % 32 of the wave's
-    // block, vocabulary entry 32 m + 8 (e / 4) + 4 (l / 32) + e % 4.
-    unsigned long long best[kFragN];
-    const int vbase = v0 + wm * kWaveM + 4 * (lane >> 5);
-    #pragma unroll
-    for (int n = 0; n < kFragN; ++n) {
-        unsigned long long b = 0ull;
-        #pragma unroll
-        for (int m = 0; m < kFragM; ++m)
-            #pragma unroll
-            for (int e = 0; e < 16; ++e) {
-                const int v = vbase + 32 * m + 8 * (e >> 2) + (e & 3);
-                const unsigned long long k = pack_key(order_key(acc[m][n][e]), (unsigned)v);
-                b = v < V ? umax64(b, k) : b;
-            }
-        best[n] = halves_max64(b);
-    }
-    // The keys of the two M-waves meet in LDS (the hidden ring, free once
-    // every wave is past its last fragment read).
-    unsigned long long *kx = reinterpret_cast<unsigned long long *>(g_lm_h);
-    __syncthreads();
-    if (wm == 1 && lane < 32) {
-        #pragma unroll
-        for (int n = 0; n < kFragN; ++n) kx[wn * kWaveN + 32 * n + lane] = best[n];
-    }
-    __syncthreads();
-    if (wm == 0 && lane < 32) {
-        #pragma unroll
-        for (int n = 0; n < kFragN; ++n) {
-            const int row = r0 + wn * kWaveN + 32 * n + lane;
-            if (row < R) atomicMax(keys + row, umax64(best[n], kx[wn * kWaveN + 32 * n + lane]));
-        }
+    int id = first, x = 0;
+    while (x < total) {
+        const int end = x + U;
+        for (; x < end && x + 2 < total; ++x) unit(x, std::true_type());
+        for (; x < end; ++x) unit(x, std::false_type());
+        lds_wait_all();                                  // the next unit's first fragments
+        ready(0);
+        fold(vt_of(id));
+        const int nid = next_id(id);
+        if (nid >= groups || rb_of(nid) != rb_of(id)) flush(rb_of(id));
+        id = nid;
     }
 }
 
@@ -634,17 +646,22 @@ hipError_t launch_lm_head_argmax_accept(const uint16_t *hidden, const uint16_t *
     const int R = B * N;
     hipError_t e = launch_kernel(lm_keys_clear_kernel, dim3((R + 255) / 256), dim3(256), s, keys, R);
     if (e != hipSuccess) return e;
-    if (R <= kStreamRows) {
-        e = launch_stream_rows(hidden, w, R, V, d, keys, s);
-        if (e != hipSuccess) return e;
+    // the tiled product's offsets inside a tile fit 32 bits only below this d
+    if (R <= kStreamRows || d >= 1 << 23) {
+        for (int r0 = 0; r0 < R; r0 += kStreamRows) {
+            e = launch_stream_rows(hidden + (size_t)r0 * d, w, R - r0 < kStreamRows ? R - r0 : kStreamRows,
+                                   V, d, keys + r0, s);
+            if (e != hipSuccess) return e;
+        }
         return launch_accept(keys, 1, draft, parent, num_nodes, B, N, argmax_out, accept_len,
                              accept_idx, bonus, s);
     }
     const int vtiles = lm_head_vocab_tiles(V);
     const int rblocks = (R + kTileN - 1) / kTileN;
     const int groups = (vtiles + kNumXcd - 1) / kNumXcd * kNumXcd * rblocks;
-    e = launch_kernel(lm_head_argmax_kernel, dim3(groups), dim3(kLmThreads), s, hidden, w, R, V, d,
-                      vtiles, rblocks, keys);
+    const int wgs = groups < 256 ? groups : 256;     // one workgroup per CU (its LDS)
+    e = launch_kernel(lm_head_argmax_kernel, dim3(wgs), dim3(kLmThreads), s, hidden, w, R, V, d,
+                      vtiles, rblocks, groups, keys);
     if (e != hipSuccess) return e;
     return launch_accept(keys, 1, draft, parent, num_nodes, B, N, argmax_out, accept_len,
                          accept_idx, bonus, s);

@@ -116,6 +116,8 @@ FEW_ROWS = [
     (1, 65, 3000, 320),        # more than 64 rows: the smallest and the largest
     (2, 64, 98400, 64),
     (3, 43, 2000, 128),        # 129 rows: the tiled product
+    (10, 60, 25700, 64),       # three row blocks, more tiles than workgroups: the block changes per tile
+    (5, 60, 33100, 192),       # two row blocks: a workgroup keeps its block over its tiles
 ]
 
 
@@ -158,6 +160,30 @@ def test_lm_head_equal_rows_pick_lowest_id(oracle_mod):
     x.w_head[low] = x.w_head[win]          # an earlier duplicate of row r's winner
     got = run_gpu(T, x)
     assert got[0].reshape(-1)[r] == min(low, win)
+
+
+def test_lm_head_tiled_special_values(oracle_mod):
+    """The tiled product's search for the lowest entry of the maximum: a hidden
+    row of zeros ties every entry at 0 (entry 0 wins), two infinite logits tie
+    at +inf (the lower one wins), a NaN entry beats both, and other rows are
+    untouched by their neighbours."""
+    T = U.require_gpu()
+    x = W.make_lm_head_inputs("special", 312, B=4, N=64, V=3000, d=128)
+    h = x.hidden.reshape(-1, x.d)
+    h[7] = 0
+    h[200] = 0
+    h[200, 5] = W.f32_to_bf16_bits(np.array([1.0], np.float32))[0]
+    x.w_head[1500, 5] = x.w_head[2900, 5] = 0x7F80            # +inf
+    keep = np.delete(np.arange(256), [7, 200])
+    h[keep, 5] = 0x8000                                       # -0 * inf = NaN
+    got = run_gpu(T, x)[0].reshape(-1)
+    assert got[7] == 1500 and got[200] == 1500                # 0 * inf = NaN; 1 * inf = inf
+    assert (got[keep] == 1500).all()
+    x.w_head[1500, 5] = x.w_head[2900, 5] = 0
+    h[keep, 5] = 0
+    got = run_gpu(T, x)[0]
+    assert got.reshape(-1)[7] == 0
+    check_argmax(oracle_mod, x, got, keep, "special")
 
 
 def test_lm_head_nan_column_wins():
