@@ -5,51 +5,78 @@
 // At step i a frontier node's children are the k most probable tokens of
 // softmax(l_i + r), r being the node token's row of the hot-token table (§5.1
 // collapses the token-info embedding into an additive logit table; §6.1 keeps
-// it for the hot tokens only). Everything about that softmax that does not
-// depend on the node -- the non-hot entries of l_i -- is reduced once per
-// (sequence, step), for all steps at once (tb_rows_kernel, one streaming pass
-// over the logits). Per step only the H hot columns are visited for each
-// frontier node (tb_expand_kernel), and one workgroup per sequence combines
-// the partial results into children, joint probabilities and the next
-// frontier (tb_select_kernel). tb_prune_kernel finally keeps the `budget`
-// nodes of largest joint probability, in creation order.
+// it for the hot tokens only). What depends on the node are the H hot columns;
+// the non-hot entries of l_i are reduced once per (sequence, step). The steps
+// depend on each other, so the number of launches and the chain inside each
+// decide the time: one launch per step (tb_step_kernel) in which
+//   * every workgroup of a sequence first combines the previous step's partial
+//     results into children, joint probabilities and the frontier, each for
+//     itself (in less time than another launch takes), then expands the
+//     frontier on its share of the hot columns;
+//   * further workgroups, on the same CUs, reduce the non-hot entries of this
+//     step, which the next launch needs.
+// tb_finish_kernel selects the last step's children and keeps the `budget`
+// nodes of largest joint probability, in creation order. Without hot tokens
+// only the rows (tb_rows_kernel) and tb_finish_kernel run.
 //
 // Decisions: candidates are ranked by the fp32 sum l + r (the precision of the
 // logits; ties to the lower vocabulary id) through a packed 64-bit key.
 // Probabilities and joint probabilities are fp64 (exp and sums in double), so
 // frontier and pruning decisions agree with an fp64 evaluation unless two
 // joint probabilities are equal to within about 1e-13.
+//
+// Top-k of a set held in registers: the maxima of k or more disjoint groups of
+// it are k candidates, so none of the k largest lies below the smallest of
+// those maxima. The entries at or above that floor (about 22 for 8 groups, 54
+// for 16) are listed in LDS and ranked by counting; a list that would overflow
+// (many equal entries) is replaced by k rounds of a plain maximum. The list holds
+// 256 entries: of 2048 random ones, fewer than one set in a million has more at
+// or above its floor. (With 64, one wave in 700 did, and its rounds set the time
+// of nearly every step: 38 us against 22.)
+//
+// Measured (16 sequences, 7 steps, vocabulary 128256, 32768 hot tokens, k 8):
+// 199 us per call with a launch for all rows and two launches per step, 157 us
+// now; 3 sequences, 5 steps, 32000 tokens, all hot, k 4: 74 -> 42 us. A step is
+// 22 us, 19 without its rows, which took 43 us of their own for the seven steps.
 #include "tv_internal.h"
 
 namespace tv {
 namespace {
 
-constexpr int kTbThreads = 256;
-constexpr int kTbChunk = 32;               // candidates per thread held in registers at once
-constexpr int kExpThreads = kWave;         // one wave per expansion workgroup: no block reduction
+constexpr int kTbThreads = 512;
 constexpr int kTbWaves = kTbThreads / kWave;
-constexpr int kPruneThreads = 1024;
+constexpr int kTbList = 4 * kWave;         // listed candidates of one wave
+constexpr int kRowsList = 512;      // listed candidates of a rows workgroup
+constexpr int kExpTab = 64;                // entries of exp_nonpos's table
+constexpr int kMaxParts = 32;              // most segments of a row, most chunks of the hot columns
 constexpr int kPruneSlots = 4096;          // >= 1 + k + (S - 1) k^2 for k, S <= 16
+constexpr int kBuckets = 1024;             // of joint probabilities, for the pruning
+constexpr float kNegInf = -__builtin_huge_valf();
 
-// One partial reduction over a set of candidates: their maximum, the sum of
-// exp(x - max) in fp64, and the top-k keys in descending order (0 = none).
-struct TbPart {
+// Partial reductions over sets of candidates, contiguous per reader: of each
+// part its maximum and the sum of exp(x - max) in fp64, its top-k keys in
+// descending order (0 = none) and, of column parts, their hot columns; kk keys
+// per part, the power of two at or above k. Part p of a row: (b S + step) segs +
+// segment; of the columns: (b k + slot) chunks + chunk.
+struct TbSum {
+    double s;
     float m;
     int pad;
-    double s;
-    unsigned long long key[kTbMaxK];
+};
+struct TbParts {
+    TbSum *sum;
+    unsigned long long *key;
+    int *col;
 };
 
 // The frontier of one sequence: its node count and, per slot (frontier order),
-// the node, its token, the token's hot row (-1: none) and its joint
-// probability -- everything the next expansion and selection need, in one
-// load (no chain through the node arrays and the hot map).
+// the node, the hot row of its token (-1: none) and its joint probability.
 struct TbSlot {
-    int node, tok, h, pad;
+    int node, h;
     double joint;
 };
 struct TbFrontier {
-    int count, pad[3];
+    int count, pad;
     TbSlot slot[kTbMaxK];
 };
 
@@ -62,6 +89,9 @@ __device__ __forceinline__ int hot_row(const int32_t *hot_index, int t, int V, i
 __device__ __forceinline__ unsigned long long umax64(unsigned long long a, unsigned long long b) {
     return a > b ? a : b;
 }
+__device__ __forceinline__ unsigned long long umin64(unsigned long long a, unsigned long long b) {
+    return a < b ? a : b;
+}
 
 __device__ __forceinline__ float key_value(unsigned long long key) {
     const unsigned int k = (unsigned int)(key >> 32);
@@ -72,36 +102,20 @@ __device__ __forceinline__ int key_index(unsigned long long key) {
     return (int)(0xFFFFFFFFu - (unsigned int)key);
 }
 
-__device__ __forceinline__ double exp_nonpos(double x, const double *tab);
+// LDS traffic of one wave between its own lanes: the writes before are done,
+// and the compiler keeps the reads behind them.
+__device__ __forceinline__ void wave_lds_sync() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
 
-// Running (max, sum of exp(x - max)) of one thread, fp64 sums; a batch of
-// values is folded in with one rescale, without per-value branches. tab: the
-// 2^(j/32) table of exp_nonpos.
-struct OnlineSum {
-    float m = -__builtin_huge_valf();
-    double s = 0.0;
-    __device__ __forceinline__ void merge(float m2, double s2, const double *tab) {
-        if (m2 == -__builtin_huge_valf()) return;
-        if (m == -__builtin_huge_valf()) { m = m2; s = s2; return; }
-        const float mn = fmaxf(m, m2);
-        s = s * exp_nonpos((double)m - (double)mn, tab) + s2 * exp_nonpos((double)m2 - (double)mn, tab);
-        m = mn;
-    }
-};
-
-// Cross-lane helpers without LDS: readlane (wave-uniform source lane) and a
-// one-lane shift inside each row of 16 lanes (DPP row_shr:1).
+// Cross-lane helpers without LDS.
 __device__ __forceinline__ unsigned long long readlane64(unsigned long long v, int src) {
     const unsigned int lo = __builtin_amdgcn_readlane((int)(unsigned int)v, src);
     const unsigned int hi = __builtin_amdgcn_readlane((int)(unsigned int)(v >> 32), src);
     return ((unsigned long long)hi << 32) | lo;
 }
 
-__device__ __forceinline__ unsigned long long row_shr1_64(unsigned long long v) {
-    const int lo = (int)(unsigned int)v, hi = (int)(unsigned int)(v >> 32);
-    const unsigned int nlo = __builtin_amdgcn_update_dpp(lo, lo, 0x111, 0xF, 0xF, false);
-    const unsigned int nhi = __builtin_amdgcn_update_dpp(hi, hi, 0x111, 0xF, 0xF, false);
-    return ((unsigned long long)nhi << 32) | nlo;
+template <int C>
+__device__ __forceinline__ unsigned int dpp32(unsigned int v) {
+    return (unsigned int)__builtin_amdgcn_update_dpp((int)v, (int)v, C, 0xF, 0xF, false);
 }
 
 // Largest 64-bit key over the wave, by a scan of per-row maxima (no LDS).
@@ -124,27 +138,11 @@ __device__ __forceinline__ unsigned long long wave_max64(unsigned long long v) {
                   umax64(readlane64(v, 47), readlane64(v, 63)));
 }
 
-// Largest 32-bit value over the wave: a scan of per-row maxima by DPP row
-// shifts, then the four rows' last lanes (no LDS).
-__device__ __forceinline__ unsigned int wave_max32(unsigned int v) {
-    v = max(v, (unsigned int)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x111, 0xF, 0xF, false));
-    v = max(v, (unsigned int)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x112, 0xF, 0xF, false));
-    v = max(v, (unsigned int)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x114, 0xF, 0xF, false));
-    v = max(v, (unsigned int)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x118, 0xF, 0xF, false));
-    // lane 15 of every row now holds its row's maximum
-    return max(max((unsigned int)__builtin_amdgcn_readlane((int)v, 15), (unsigned int)__builtin_amdgcn_readlane((int)v, 31)),
-               max((unsigned int)__builtin_amdgcn_readlane((int)v, 47), (unsigned int)__builtin_amdgcn_readlane((int)v, 63)));
-}
-
 // Whole-wave reductions without LDS: butterflies inside each row of 16 lanes
 // by DPP (swap neighbours, swap pairs, mirror each half row, mirror the row:
 // after each step every lane of the group holds the group's result), then
 // across rows by the row-pair and half-wave swaps. Every lane ends with the
 // result.
-template <int C>
-__device__ __forceinline__ unsigned int dpp32(unsigned int v) {
-    return (unsigned int)__builtin_amdgcn_update_dpp((int)v, (int)v, C, 0xF, 0xF, false);
-}
 template <int C>
 __device__ __forceinline__ double dpp64(double v) {
     const unsigned long long b = (unsigned long long)__double_as_longlong(v);
@@ -193,149 +191,175 @@ __device__ __forceinline__ int group_sum(int v, int n) {
     return v;
 }
 
-// A wave's top-k list, distributed over lanes: lane j < k holds the (j+1)-th
-// largest key seen by the wave (0 = empty). The k-th key is the wave's
-// admission threshold, so after the first few batches almost no candidate
-// needs more than one compare; an admitted key is inserted by one shift.
-struct WaveTopK {
-    unsigned long long w = 0ull;      // this lane's entry
-    unsigned long long thr = 0ull;    // the k-th entry (wave-uniform)
-    __device__ __forceinline__ void offer(unsigned long long cand, int k, int lane) {
-        unsigned long long mask = __ballot(cand > thr);
-        while (mask) {                                   // wave-uniform
-            const int src = __builtin_ctzll(mask);
-            const unsigned long long cc = readlane64(cand, src);
-            const int pos = __popcll(__ballot(lane < k && w > cc));   // entries above cc
-            const unsigned long long up = row_shr1_64(w);
-            if (lane < k) w = lane == pos ? cc : (lane > pos ? up : w);
-            thr = readlane64(w, k - 1);
-            mask &= ~(1ull << src);
-            mask &= __ballot(cand > thr);
-        }
+
+template <int C>
+__device__ __forceinline__ unsigned long long dpp64u(unsigned long long v) {
+    return ((unsigned long long)dpp32<C>((unsigned int)(v >> 32)) << 32) | dpp32<C>((unsigned int)v);
+}
+
+// Smallest of the maxima of 8 groups of 8 lanes (k <= 8) or 16 groups of 4:
+// at least k of the lanes' values are at or above it.
+__device__ __forceinline__ float wave_floor(float v, int k) {
+    const auto mx = [](float a, unsigned b) { return fmaxf(a, __uint_as_float(b)); };
+    const auto mn = [](float a, unsigned b) { return fminf(a, __uint_as_float(b)); };
+    v = mx(v, dpp32<kDppXor1>(__float_as_uint(v)));
+    v = mx(v, dpp32<kDppXor2>(__float_as_uint(v)));
+    const unsigned hm = dpp32<kDppHalfMirror>(__float_as_uint(v));
+    v = k <= 8 ? mx(v, hm) : mn(v, hm);
+    v = mn(v, dpp32<kDppMirror>(__float_as_uint(v)));
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = mn(__uint_as_float(r[0]), r[1]);
+    const auto h = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return mn(__uint_as_float(h[0]), h[1]);
+}
+__device__ __forceinline__ unsigned long long wave_floor64(unsigned long long v, int k) {
+    v = umax64(v, dpp64u<kDppXor1>(v));
+    v = umax64(v, dpp64u<kDppXor2>(v));
+    const unsigned long long hm = dpp64u<kDppHalfMirror>(v);
+    v = k <= 8 ? umax64(v, hm) : umin64(v, hm);
+    v = umin64(v, dpp64u<kDppMirror>(v));
+    #pragma unroll
+    for (int half = 0; half < 2; ++half) {
+        const unsigned int lo = (unsigned int)v, hi = (unsigned int)(v >> 32);
+        const auto l = half == 0 ? __builtin_amdgcn_permlane16_swap(lo, lo, false, false)
+                                 : __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
+        const auto h = half == 0 ? __builtin_amdgcn_permlane16_swap(hi, hi, false, false)
+                                 : __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+        v = umin64(((unsigned long long)h[0] << 32) | l[0], ((unsigned long long)h[1] << 32) | l[1]);
     }
+    return v;
+}
+
+// Lanes of `mask` below this one.
+__device__ __forceinline__ int below(unsigned long long mask) {
+    return (int)__builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)mask, 0u));
+}
+
+// 2^(j/64), j = 0..63, rounded to nearest.
+__device__ const double kExp2Table[kExpTab] = {
+    0x1.0000000000000p+0, 0x1.02c9a3e778061p+0, 0x1.059b0d3158574p+0,
+    0x1.0874518759bc8p+0, 0x1.0b5586cf9890fp+0, 0x1.0e3ec32d3d1a2p+0,
+    0x1.11301d0125b51p+0, 0x1.1429aaea92de0p+0, 0x1.172b83c7d517bp+0,
+    0x1.1a35beb6fcb75p+0, 0x1.1d4873168b9aap+0, 0x1.2063b88628cd6p+0,
+    0x1.2387a6e756238p+0, 0x1.26b4565e27cddp+0, 0x1.29e9df51fdee1p+0,
+    0x1.2d285a6e4030bp+0, 0x1.306fe0a31b715p+0, 0x1.33c08b26416ffp+0,
+    0x1.371a7373aa9cbp+0, 0x1.3a7db34e59ff7p+0, 0x1.3dea64c123422p+0,
+    0x1.4160a21f72e2ap+0, 0x1.44e086061892dp+0, 0x1.486a2b5c13cd0p+0,
+    0x1.4bfdad5362a27p+0, 0x1.4f9b2769d2ca7p+0, 0x1.5342b569d4f82p+0,
+    0x1.56f4736b527dap+0, 0x1.5ab07dd485429p+0, 0x1.5e76f15ad2148p+0,
+    0x1.6247eb03a5585p+0, 0x1.6623882552225p+0, 0x1.6a09e667f3bcdp+0,
+    0x1.6dfb23c651a2fp+0, 0x1.71f75e8ec5f74p+0, 0x1.75feb564267c9p+0,
+    0x1.7a11473eb0187p+0, 0x1.7e2f336cf4e62p+0, 0x1.82589994cce13p+0,
+    0x1.868d99b4492edp+0, 0x1.8ace5422aa0dbp+0, 0x1.8f1ae99157736p+0,
+    0x1.93737b0cdc5e5p+0, 0x1.97d829fde4e50p+0, 0x1.9c49182a3f090p+0,
+    0x1.a0c667b5de565p+0, 0x1.a5503b23e255dp+0, 0x1.a9e6b5579fdbfp+0,
+    0x1.ae89f995ad3adp+0, 0x1.b33a2b84f15fbp+0, 0x1.b7f76f2fb5e47p+0,
+    0x1.bcc1e904bc1d2p+0, 0x1.c199bdd85529cp+0, 0x1.c67f12e57d14bp+0,
+    0x1.cb720dcef9069p+0, 0x1.d072d4a07897cp+0, 0x1.d5818dcfba487p+0,
+    0x1.da9e603db3285p+0, 0x1.dfc97337b9b5fp+0, 0x1.e502ee78b3ff6p+0,
+    0x1.ea4afa2a490dap+0, 0x1.efa1bee615a27p+0, 0x1.f50765b6e4540p+0,
+    0x1.fa7c1819e90d8p+0,
 };
 
 // exp(x) for x <= 0 in double precision, by Tang's table-driven method (ACM
-// TOMS 15(2), 1989): x = (32 n + j) ln2/32 + r with |r| <= ln2/64, so
-// e^x = 2^(n >> 5) 2^(j/32) e^r, j = n & 31; e^r - 1 from its degree-6 Taylor
-// polynomial (truncation below 2e-17 on that interval); 2^(j/32) from a
-// 32-entry table (tab, filled by fill_exp2_table). ln2/32 is split into
-// kL1 (its 37 leading significant bits, so N kL1 is exact for |N| < 2^16) and
-// kL2 = ln2/32 - kL1 rounded to double. Arguments below -745 (and -inf) give 0.
-// About 1 ulp, against about 45 instructions for the library's exp.
+// TOMS 15(2), 1989): x = (64 n + j) ln2/64 + r with |r| <= ln2/128, so
+// e^x = 2^n 2^(j/64) e^r; e^r - 1 from its degree-5 Taylor polynomial
+// (truncation below 4e-17 on that interval); 2^(j/64) from a table (tab, a copy
+// of kExp2Table in LDS). ln2/64 is split into kL1 (its 37 leading significant
+// bits, so N kL1 is exact for |N| < 2^16) and kL2 = ln2/64 - kL1 rounded to
+// double. N is rounded by adding 1.5 2^52, whose low word then holds it.
+// Arguments below -700 (and -inf, NaN) count as -700: 1e-304, below any
+// rounding of a sum whose largest term is 1. About 1 ulp.
 __device__ __forceinline__ double exp_nonpos(double x, const double *tab) {
-    const double kInvL = 46.16624130844683;          // 32 / ln2
-    const double kL1 = 0.021660849392446835;
-    const double kL2 = 5.145609244655338e-14;
-    const double N = __builtin_rint(x * kInvL);
+    const double kInvL = 92.33248261689366;          // 64 / ln2
+    const double kL1 = 0.010830424696223417;
+    const double kL2 = 2.572804622327669e-14;
+    const double kRound = 6755399441055744.0;
+    x = __builtin_fmax(x, -700.0);
+    const double z = __builtin_fma(x, kInvL, kRound);
+    const double N = z - kRound;
     double r = __builtin_fma(-N, kL1, x);
     r = __builtin_fma(-N, kL2, r);
-    double q = __builtin_fma(r, 1.0 / 720.0, 1.0 / 120.0);
-    q = __builtin_fma(q, r, 1.0 / 24.0);
+    double q = __builtin_fma(r, 1.0 / 120.0, 1.0 / 24.0);
     q = __builtin_fma(q, r, 1.0 / 6.0);
     q = __builtin_fma(q, r, 0.5);
     q = __builtin_fma(q, r, 1.0);
     q *= r;                                          // e^r - 1
-    const int n = x < -745.0 ? 0 : (int)N;
-    const double t = tab[n & 31];
-    const double y = __builtin_ldexp(__builtin_fma(t, q, t), n >> 5);
-    return x < -745.0 ? 0.0 : y;
+    const unsigned int n = (unsigned int)__double_as_longlong(z);
+    const unsigned long long t0 = (unsigned long long)__double_as_longlong(tab[n & (kExpTab - 1)]);
+    const unsigned int hi = (unsigned int)(t0 >> 32) + ((n << 14) & 0xFFF00000u);
+    const double t = __longlong_as_double((long long)(((unsigned long long)hi << 32) | (unsigned int)t0));
+    return __builtin_fma(t, q, t);
 }
 
-// 2^(j/32), j = 0..31, into LDS for exp_nonpos; the caller synchronises.
+// The table into LDS for exp_nonpos; the caller synchronises.
 __device__ __forceinline__ void fill_exp2_table(double *tab) {
-    if (threadIdx.x < 32) tab[threadIdx.x] = exp2((double)threadIdx.x / 32.0);
+    if (threadIdx.x < kExpTab) tab[threadIdx.x] = kExp2Table[threadIdx.x];
 }
 
-// One chunk of a thread's candidates, all in registers: x[u] is the value of
-// vocabulary id id(u), -inf when it is not a candidate. Folds their
-// (max, fp64 sum of exp(x - max)) into os and their k largest keys into the
-// wave's list. The wave's k largest are all at or above the k-th largest of
-// the lanes' maxima (those are k candidates already), so only candidates at or
-// above that floor form keys and go through the wave-serial insertion.
-template <int U, typename Id>
-__device__ __forceinline__ void fold_chunk(const float (&x)[U], Id id, int k, int lane,
-                                           const double *tab, OnlineSum &os, WaveTopK &tk) {
-    constexpr float kNegInf = -__builtin_huge_valf();
-    float m = kNegInf;
-    unsigned int kv[U];
-    unsigned int kmax = 0u;
-    #pragma unroll
-    for (int u = 0; u < U; ++u) {
-        m = fmaxf(m, x[u]);
-        kv[u] = x[u] != kNegInf ? order_key(x[u]) : 0u;
-        kmax = max(kmax, kv[u]);
-    }
-    if (m != kNegInf) {
-        double sum = 0.0;
+template <typename T>
+__device__ __forceinline__ void tie(T &x) {
+    asm volatile("" : "+v"(x));
+}
+
+// How many of list[0 .. n) exceed `a` and `b`. The list is readable and zero (no
+// key) up to the next multiple of 8; eight reads are in flight together.
+__device__ __forceinline__ void count_above(const unsigned long long *list, int n, unsigned long long a,
+                                            unsigned long long b, int &ra, int &rb) {
+    for (int i = 0; i < n; i += 8) {
+        unsigned long long o[8];
         #pragma unroll
-        for (int u = 0; u < U; ++u) sum += exp_nonpos((double)x[u] - (double)m, tab);
-        os.merge(m, sum, tab);
-    }
-    // k-th largest lane maximum (ties may remove two lanes in one round: the
-    // floor only gets lower, never wrong); once the wave's list is full, its
-    // k-th key is a floor already and the rounds are skipped
-    unsigned int floor_key = (unsigned int)(tk.thr >> 32);
-    if (floor_key == 0u) {
-        for (int r = 0; r < k; ++r) {
-            const unsigned int mx = wave_max32(kmax);
-            if (kmax == mx) kmax = 0u;
-            floor_key = mx;
-        }
-    }
-    #pragma unroll
-    for (int u = 0; u < U; ++u) {
-        const bool pass = kv[u] != 0u && kv[u] >= floor_key;
-        if (__ballot(pass) == 0ull) continue;                 // wave-uniform
-        tk.offer(pass ? pack_key(kv[u], (unsigned int)id(u)) : 0ull, k, lane);
-    }
-}
-
-// Workgroup reduction of every thread's OnlineSum and every wave's top-k list
-// into one TbPart.
-__device__ void block_reduce_part(OnlineSum os, const WaveTopK &tk, int k, TbPart *out,
-                                  const double *tab) {
-    __shared__ float s_m[kTbWaves];
-    __shared__ double s_s[kTbWaves];
-    __shared__ unsigned long long s_key[kTbWaves * kTbMaxK];
-    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-    // the wave's maximum first, then each lane's sum rescaled to it once and
-    // the sums added (one exponential per lane instead of one per merge)
-    const float wm = wave_allmax(os.m);
-    const double ws = wave_allsum(os.m == -__builtin_huge_valf() ? 0.0 : os.s * exp_nonpos((double)os.m - (double)wm, tab));
-    os.m = wm;
-    os.s = ws;
-    if (lane == 0) { s_m[wave] = os.m; s_s[wave] = os.s; }
-    if (lane < kTbMaxK) s_key[wave * kTbMaxK + lane] = lane < k ? tk.w : 0ull;
-    __syncthreads();
-    if (wave == 0) {
-        // the k largest of the waves' lists: one candidate per lane
-        unsigned long long c = lane < kTbWaves * kTbMaxK ? s_key[lane] : 0ull;
-        for (int r = 0; r < k; ++r) {
-            const unsigned long long best = wave_max64(c);
-            if (c == best) c = 0ull;
-            if (lane == 0) out->key[r] = best;
-        }
-        if (lane == 0) {
-            for (int r = k; r < kTbMaxK; ++r) out->key[r] = 0ull;
-            OnlineSum t;
-            for (int w = 0; w < kTbWaves; ++w) t.merge(s_m[w], s_s[w], tab);
-            out->m = t.m;
-            out->pad = 0;
-            out->s = t.s;
+        for (int u = 0; u < 8; ++u) o[u] = list[i + u];
+        #pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            ra += o[u] > a;
+            rb += o[u] > b;
         }
     }
 }
 
-// One wave's OnlineSum and top-k list into one TbPart (the wave maximum first,
-// then each lane's sum rescaled to it once; the list is already in lanes
-// 0..k-1).
-__device__ __forceinline__ void wave_reduce_part(const OnlineSum &os, const WaveTopK &tk, int k,
-                                                 int lane, TbPart *out, const double *tab) {
-    const float wm = wave_allmax(os.m);
-    const double ws = wave_allsum(os.m == -__builtin_huge_valf() ? 0.0 : os.s * exp_nonpos((double)os.m - (double)wm, tab));
-    if (lane == 0) { out->m = wm; out->pad = 0; out->s = ws; }
-    if (lane < kTbMaxK) out->key[lane] = lane < k ? tk.w : 0ull;
+// The k largest of a wave's list[0 .. n) (room for 8 more entries) and, with
+// `more`, of the k keys in old, in descending order into win (0 = none), with
+// their columns. By one wave, which has synchronised its LDS writes; it is
+// synchronised again on return.
+__device__ __forceinline__ void list_winners(unsigned long long *list, const int *lcol, int n, int k, int lane,
+                                             bool more, const unsigned long long *old, const int *ocol,
+                                             unsigned long long *win, int *wcol) {
+    if (lane < 8) list[n + lane] = 0ull;
+    if (lane < kTbMaxK) win[lane] = 0ull;
+    wave_lds_sync();
+    unsigned long long prev = more && lane < k ? old[lane] : 0ull;
+    int prank = 0;
+    for (int b0 = 0; b0 < n; b0 += kWave) {          // one round unless the list is long
+        const unsigned long long mine = b0 + lane < n ? list[b0 + lane] : 0ull;
+        const int col = lcol[min(b0 + lane, n - 1)];
+        int rank = 0, unused = 0;
+        count_above(list, n, mine, ~0ull, rank, unused);
+        if (more) count_above(old, k, mine, ~0ull, rank, unused);
+        if (mine != 0ull && rank < k) {
+            win[rank] = mine;
+            wcol[rank] = col;
+        }
+    }
+    if (more) {
+        int unused = 0;
+        count_above(list, n, prev, ~0ull, prank, unused);
+        count_above(old, k, prev, ~0ull, prank, unused);
+        if (prev != 0ull && prank < k) {
+            win[prank] = prev;
+            wcol[prank] = ocol[lane];
+        }
+    }
+    wave_lds_sync();
+}
+
+// (m, s) += (m2, s2), s being a sum of exp(x - m).
+__device__ __forceinline__ void merge_sum(float &m, double &s, float m2, double s2, const double *tab) {
+    if (m2 == kNegInf) return;
+    if (m == kNegInf) { m = m2; s = s2; return; }
+    const float mn = fmaxf(m, m2);
+    s = s * exp_nonpos((double)m - (double)mn, tab) + s2 * exp_nonpos((double)m2 - (double)mn, tab);
+    m = mn;
 }
 
 // Steps of sequence b: logits rows [first, first + count). A first tree uses all
@@ -356,240 +380,272 @@ __device__ __forceinline__ TbWindow tb_window(const int32_t *accept_len, int b, 
     return {min(a, S), remain > r ? remain : 0};
 }
 
-// Node-independent part of every (sequence, step): the non-hot tokens of the
-// step's logits, one segment of the vocabulary per workgroup. Workgroup
-// (row (b, 0), segment 0) also places the root and the first frontier.
-__global__ __launch_bounds__(kTbThreads) void tb_rows_kernel(
-    const float *__restrict__ logits, const int32_t *__restrict__ hot_vocab,
-    const int32_t *__restrict__ hot_index, const int32_t *__restrict__ root_token,
-    const int32_t *__restrict__ accept_len, int r, int S, int V, int H, int k, int seg_len,
-    TbPart *__restrict__ rows, float *__restrict__ hot_logits, int max_nodes,
-    int32_t *__restrict__ node_tok, int32_t *__restrict__ node_par,
-    double *__restrict__ node_joint, TbFrontier *__restrict__ frontier) {
-    __shared__ double s_exp2[32];
+// LDS of a rows reduction.
+struct RowsShared {
+    double exp2[kExpTab];
+    float gm[2 * kTbWaves];                          // group maxima: waves, or half waves
+    double sum[kTbWaves];
+    unsigned long long list[kRowsList], best[kTbWaves], win[kTbMaxK];
+    int n;
+};
+
+// Node-independent part of one (sequence, step): the non-hot tokens of the
+// step's logits, one segment of the vocabulary per workgroup, in passes of U
+// tokens per thread held in registers (one pass unless the vocabulary is larger
+// than 32 segments of them). Bound by its instructions (about 35 per token, two
+// thirds of them the fp64 exponential), not by the logits' bytes.
+template <int U>
+__device__ __forceinline__ void reduce_row(RowsShared &sh, const float *__restrict__ l,
+                                           const int32_t *__restrict__ hot_index, int V, int H, int k, int kk,
+                                           int v0, int v1, TbSum *sum_out, unsigned long long *key_out) {
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+    double *const s_exp2 = sh.exp2, *const s_sum = sh.sum;
+    float *const s_gm = sh.gm;
+    unsigned long long *const s_list = sh.list, *const s_best = sh.best, *const s_win = sh.win;
+    int &s_n = sh.n;
     fill_exp2_table(s_exp2);
-    __syncthreads();
-    const int row = blockIdx.x, seg = blockIdx.y;
-    const int v0 = seg * seg_len, v1 = min(V, v0 + seg_len);
-    const float *l = logits + (size_t)row * V;
-    OnlineSum os;
-    WaveTopK tk;
-    const int lane = threadIdx.x & (kWave - 1);
-    // Chunks of kTbChunk tokens per thread, every load of a chunk issued before
-    // any is used (indices clamped, so the loads are unconditional). The chunk
-    // loop is uniform over the workgroup (the wave's list is updated by
-    // whole-wave steps).
-    const int iters = (max(v1 - v0, 0) + kTbThreads - 1) / kTbThreads;
-    for (int it0 = 0; it0 < iters; it0 += kTbChunk) {
-        const int vb = v0 + it0 * kTbThreads + (int)threadIdx.x;
-        int hv[kTbChunk];
-        float xv[kTbChunk];
-        #pragma unroll
-        for (int u = 0; u < kTbChunk; ++u) {
-            const int v = min(vb + u * kTbThreads, v1 - 1);
-            hv[u] = H > 0 ? hot_index[v] : -1;
-            xv[u] = l[v];
-        }
-        #pragma unroll
-        for (int u = 0; u < kTbChunk; ++u) {     // outside, or hot (handled per node): unused
-            const bool use = vb + u * kTbThreads < v1 && !(hv[u] >= 0 && hv[u] < H);
-            xv[u] = use ? xv[u] : -__builtin_huge_valf();
-        }
-        fold_chunk(xv, [&](int u) { return vb + u * kTbThreads; }, k, lane, s_exp2, os, tk);
-    }
-    block_reduce_part(os, tk, k, rows + (size_t)row * gridDim.y + seg, s_exp2);
-    // this row's logits of the hot tokens, contiguous for the per-node passes
-    if (H > 0) {
-        const int c_len = (H + gridDim.y - 1) / gridDim.y;
-        const int c0 = seg * c_len, c1 = min(H, c0 + c_len);
-        float *lh = hot_logits + (size_t)row * H;
-        constexpr int kG = 8;                        // gathers per thread in flight together
-        for (int cb = c0 + (int)threadIdx.x; cb < c1; cb += kG * kTbThreads) {
-            int hv[kG];
-            float hx[kG];
+    if (tid < kTbMaxK) s_win[tid] = 0ull;
+    float M = kNegInf;                               // thread 0: the segment so far
+    double sum = 0.0;
+    for (int vb = v0; vb < v1; vb += U * kTbThreads) {
+        float xv[U];
+        {
+            int hv[U];
             #pragma unroll
-            for (int u = 0; u < kG; ++u) {
-                const int c = cb + u * kTbThreads;
-                hv[u] = c < c1 ? hot_vocab[c] : -1;
+            for (int u = 0; u < U; ++u) {            // every load before any use (indices clamped)
+                const int v = min(vb + u * kTbThreads + tid, v1 - 1);
+                hv[u] = H > 0 ? hot_index[v] : -1;
+                xv[u] = l[v];
             }
             #pragma unroll
-            for (int u = 0; u < kG; ++u) hx[u] = (hv[u] >= 0 && hv[u] < V) ? l[hv[u]] : -__builtin_huge_valf();
-            #pragma unroll
-            for (int u = 0; u < kG; ++u)
-                if (cb + u * kTbThreads < c1) lh[cb + u * kTbThreads] = hx[u];
+            for (int u = 0; u < U; ++u) {            // outside, or hot (handled per node): unused
+                xv[u] = (unsigned)hv[u] >= (unsigned)H ? xv[u] : kNegInf;
+                xv[u] = tid < v1 - vb - u * kTbThreads ? xv[u] : kNegInf;
+                tie(xv[u]);                          // one mask at a time
+            }
+        }
+        float m = kNegInf;
+        #pragma unroll
+        for (int u = 0; u < U; ++u) m = fmaxf(m, xv[u]);
+        __syncthreads();                             // the previous pass's lists are done with
+        if (tid == 0) s_n = 0;
+        {
+            // group maxima: the waves' for k <= 8, their halves' above
+            m = fmaxf(m, __uint_as_float(dpp32<kDppXor1>(__float_as_uint(m))));
+            m = fmaxf(m, __uint_as_float(dpp32<kDppXor2>(__float_as_uint(m))));
+            m = fmaxf(m, __uint_as_float(dpp32<kDppHalfMirror>(__float_as_uint(m))));
+            m = fmaxf(m, __uint_as_float(dpp32<kDppMirror>(__float_as_uint(m))));
+            const auto x = __builtin_amdgcn_permlane16_swap(__float_as_uint(m), __float_as_uint(m), false, false);
+            m = fmaxf(__uint_as_float(x[0]), __uint_as_float(x[1]));
+            if (k <= 8) {
+                const auto h = __builtin_amdgcn_permlane32_swap(__float_as_uint(m), __float_as_uint(m), false, false);
+                m = fmaxf(__uint_as_float(h[0]), __uint_as_float(h[1]));
+            }
+            if ((lane & 31) == 0) s_gm[wave * 2 + (lane >> 5)] = m;
+        }
+        __syncthreads();
+        float pm = kNegInf, fl = -kNegInf;
+        #pragma unroll
+        for (int g = 0; g < 2 * kTbWaves; ++g) {
+            pm = fmaxf(pm, s_gm[g]);
+            fl = fminf(fl, s_gm[g]);
+        }
+        if (pm == kNegInf) continue;                 // uniform: no candidate in this pass
+        fl = fmaxf(fl, -__FLT_MAX__);                // -inf is no candidate
+        double ps = 0.0;
+        #pragma unroll
+        for (int u = 0; u < U; ++u) ps += exp_nonpos((double)xv[u] - (double)pm, s_exp2);
+        ps = wave_allsum(ps);
+        if (lane == 0) s_sum[wave] = ps;
+        #pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const unsigned long long mask = __ballot(xv[u] >= fl);
+            if (mask == 0ull) continue;              // wave-uniform
+            int at = 0;
+            if (lane == 0) at = atomicAdd(&s_n, __popcll(mask));
+            at = __builtin_amdgcn_readfirstlane(at) + below(mask);
+            if (((mask >> lane) & 1ull) && at < kRowsList)
+                s_list[at] = pack_key(order_key(xv[u]), (unsigned)(vb + u * kTbThreads + tid));
+        }
+        __syncthreads();
+        const int n = s_n;
+        if (n > kRowsList) {
+            // too many at the floor: k rounds of the workgroup's largest key
+            // below the previous one (read again: keys in registers would cost the
+            // common path its registers)
+            unsigned long long prev = ~0ull;
+            for (int q = 0; q < k; ++q) {
+                unsigned long long best = 0ull;
+                #pragma unroll 1
+                for (int v = vb + tid; v < min(v1, vb + U * kTbThreads); v += kTbThreads) {
+                    if (H > 0 && (unsigned)hot_index[v] < (unsigned)H) continue;
+                    const unsigned long long key = pack_key(order_key(l[v]), (unsigned)v);
+                    best = key < prev ? umax64(best, key) : best;
+                }
+                best = wave_max64(best);
+                if (lane == 0) s_best[wave] = best;
+                __syncthreads();
+                prev = 0ull;
+                #pragma unroll
+                for (int w = 0; w < kTbWaves; ++w) prev = umax64(prev, s_best[w]);
+                __syncthreads();
+                if (tid == 0) s_list[q] = prev;
+            }
+            __syncthreads();
+        }
+        // rank the listed keys and the earlier passes' winners by counting
+        const int nl = n > kRowsList ? k : n;
+        if (tid < 8 && nl + tid < kRowsList) s_list[nl + tid] = 0ull;
+        __syncthreads();
+        const bool more = vb > v0;                   // earlier passes exist
+        unsigned long long mine = tid < nl ? s_list[tid] : 0ull;
+        unsigned long long old = (more && tid < k) ? s_win[tid] : 0ull;
+        int rank = 0, orank = 0;
+        if (wave * kWave < nl || more) {
+            count_above(s_list, nl, mine, old, rank, orank);
+            if (more) count_above(s_win, k, mine, old, rank, orank);
+        }
+        __syncthreads();
+        if (tid < kTbMaxK) s_win[tid] = 0ull;
+        __syncthreads();
+        if (mine != 0ull && rank < k) s_win[rank] = mine;
+        if (old != 0ull && orank < k) s_win[orank] = old;
+        if (tid == 0) {
+            double t = 0.0;
+            for (int w = 0; w < kTbWaves; ++w) t += s_sum[w];
+            merge_sum(M, sum, pm, t, s_exp2);
         }
     }
-    if (seg == 0 && row % S == 0 && threadIdx.x == 0) {
-        const int b = row / S;
-        node_tok[(size_t)b * max_nodes] = root_token[b];
-        node_par[(size_t)b * max_nodes] = -1;
-        node_joint[(size_t)b * max_nodes] = 1.0;
-        const int t = root_token[b];
-        TbFrontier *fr = frontier + b;
-        fr->count = tb_window(accept_len, b, S, r).count > 0 ? 1 : 0;
-        fr->slot[0] = TbSlot{0, t, hot_row(hot_index, t, V, H), 0, 1.0};
+    __syncthreads();
+    if (tid < kk) key_out[tid] = s_win[tid];
+    if (tid == 0) {
+        sum_out->s = sum;
+        sum_out->m = M;
     }
 }
 
-// Hot columns of step i for frontier slot j of sequence b, one chunk of the
-// columns per workgroup: x = l_i[hot[c]] + table[row of the node's token][c].
-__global__ __launch_bounds__(kExpThreads) void tb_expand_kernel(
-    const float *__restrict__ hot_logits, const uint16_t *__restrict__ table,
-    const int32_t *__restrict__ hot_vocab, const int32_t *__restrict__ accept_len, int r, int S,
-    int V, int H, int k, int step, int chunk_len, const TbFrontier *__restrict__ frontier,
-    TbPart *__restrict__ parts) {
-    const int b = blockIdx.x, j = blockIdx.y, c = blockIdx.z;
-    const TbFrontier *fr = frontier + b;
-    TbPart *out = parts + ((size_t)b * k + j) * gridDim.z + c;
-    const int count = fr->count;
-    const int h = fr->slot[j].h;                   // loaded with the count (j < kTbMaxK)
-    const TbWindow win = tb_window(accept_len, b, S, r);
-    if (step >= win.count) return;                 // this sequence's tree is complete
-    if (j >= count) return;                        // no such frontier node at this step
-    __shared__ double s_exp2[32];
-    fill_exp2_table(s_exp2);
-    __syncthreads();
-    const float *lh = hot_logits + ((size_t)b * S + win.first + step) * H;
-    const uint16_t *trow = table + (size_t)max(h, 0) * H;   // row 0 stands in when h < 0 (unused)
-    const int c0 = c * chunk_len, c1 = min(H, c0 + chunk_len);
-    OnlineSum os;
-    WaveTopK tk;
-    const int lane = threadIdx.x & (kWave - 1);
-    const int iters = (max(c1 - c0, 0) + kExpThreads - 1) / kExpThreads;   // chunks as above
-    for (int it0 = 0; it0 < iters; it0 += kTbChunk) {
-        const int cb = c0 + it0 * kExpThreads + (int)threadIdx.x;
-        // a full chunk needs no per-candidate range tests (kept out of the
-        // common path: they cost registers and instructions)
-        auto chunk = [&](auto full) {
-            int vv[kTbChunk];
-            float xv[kTbChunk];
-            unsigned int rv[kTbChunk];
-            if constexpr (full) {
-                // four consecutive columns per lane and load (16-byte loads of
-                // the logits and ids, 8-byte loads of the table entries)
-                const int cq = c0 + it0 * kExpThreads + 4 * lane;
-                #pragma unroll
-                for (int q = 0; q < kTbChunk / 4; ++q) {
-                    const int cc = cq + q * 4 * kExpThreads;
-                    const i32x4 v4 = *reinterpret_cast<const i32x4 *>(hot_vocab + cc);
-                    const f32x4 x4 = *reinterpret_cast<const f32x4 *>(lh + cc);
-                    const u16x4 t4 = *reinterpret_cast<const u16x4 *>(trow + cc);
-                    #pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        vv[4 * q + r] = v4[r];
-                        xv[4 * q + r] = x4[r];
-                        rv[4 * q + r] = t4[r];
-                    }
-                }
-            } else {
-                #pragma unroll
-                for (int u = 0; u < kTbChunk; ++u) {
-                    const int cc = min(cb + u * kExpThreads, c1 - 1);
-                    vv[u] = hot_vocab[cc];
-                    xv[u] = lh[cc];
-                    rv[u] = trow[cc];
-                }
-            }
-            #pragma unroll
-            for (int u = 0; u < kTbChunk; ++u) {
-                if (h >= 0) xv[u] += __uint_as_float(rv[u] << 16);
-                const bool use = (full || cb + u * kExpThreads < c1) && (unsigned int)vv[u] < (unsigned int)V;
-                xv[u] = use ? xv[u] : -__builtin_huge_valf();
-            }
-            fold_chunk(xv, [&](int u) { return vv[u]; }, k, lane, s_exp2, os, tk);
-        };
-        // full: every column of the chunk exists, and rows, chunk start, the
-        // caller's arrays and the workspace row are aligned for the wide loads
-        if (c1 - (c0 + it0 * kExpThreads) >= kTbChunk * kExpThreads && (H & 3) == 0 && (c0 & 3) == 0 &&
-            (reinterpret_cast<uintptr_t>(hot_vocab) & 15) == 0 && (reinterpret_cast<uintptr_t>(table) & 7) == 0 &&
-            (reinterpret_cast<uintptr_t>(lh) & 15) == 0)
-            chunk(std::true_type{});
-        else
-            chunk(std::false_type{});
-    }
-    wave_reduce_part(os, tk, k, lane, out, s_exp2);
-}
+// LDS of a selection.
+struct SelShared {
+    double joint[kTbMaxK * kTbMaxK];                 // the step's children
+    int col[kTbMaxK * kTbMaxK];
+    unsigned long long list[kTbWaves][kTbList + 8];  // candidates of a wave; also the expansion's
+    int lcol[kTbWaves][kTbList];
+    unsigned long long win[2][kTbWaves][kTbMaxK];    // its k largest
+    int wcol[2][kTbWaves][kTbMaxK];
+    TbSlot slot[kTbMaxK];                            // the next frontier
+    int nf;
+};
 
-// One workgroup per sequence, one wave per frontier node of step i: combine the
-// step's row partials with the node's column partials (all loaded at once)
-// into its k children (token, probability, joint probability), then choose
-// the next frontier.
-template <int CPL>          // candidate keys per lane: (segs + chunks) * k <= 64 * CPL
-__global__ __launch_bounds__(kTbMaxK * kWave) void tb_select_kernel(
-    const TbPart *__restrict__ rows, int segs, const TbPart *__restrict__ parts, int chunks,
-    const int32_t *__restrict__ accept_len, const int32_t *__restrict__ hot_index, int r, int S,
-    int V, int H, int k, int step, int max_nodes, int32_t *__restrict__ node_tok,
-    int32_t *__restrict__ node_par, double *__restrict__ node_joint,
-    TbFrontier *__restrict__ frontier) {
-    constexpr int kCandPerLane = CPL;
-    __shared__ double s_joint[kTbMaxK * kTbMaxK];
-    __shared__ int s_tok[kTbMaxK * kTbMaxK];
-    __shared__ int s_hot[kTbMaxK * kTbMaxK];
-    const int b = blockIdx.x;
-    const int lane = threadIdx.x & (kWave - 1), j = threadIdx.x / kWave;
-    const TbWindow win = tb_window(accept_len, b, S, r);
-    if (step >= win.count) return;                 // uniform: this sequence is done
-    TbFrontier *fr = frontier + b;
-    const int nf = fr->count;
+// Selection of step `step` of sequence b by a whole workgroup: per frontier
+// node (one wave each) the step's row partials and the node's column partials
+// become its k children (token, probability, joint probability), then the k
+// children of largest joint probability become the next frontier (sh.slot,
+// sh.nf). `writer`: this workgroup stores the children and the next frontier.
+// `between` runs once, after the first loads are issued, and the workgroup
+// synchronises behind it (it may fill tab) and before the return.
+template <int CPL, typename F>      // candidate keys per lane
+__device__ __forceinline__ void select_step(SelShared &sh, TbParts rows, int segs, TbParts parts, int chunks,
+                                            TbWindow win, int b, int S, int k, int step,
+                                            int max_nodes, const TbFrontier *fr, TbFrontier *next,
+                                            bool writer, const double *tab, int32_t *node_tok,
+                                            int32_t *node_par, double *node_joint, F between) {
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+    const int nparts = segs + chunks;
     // nodes before this step: the root, then k children per frontier node of
     // every earlier step (1 at step 0, k afterwards)
     const int base = step == 0 ? 1 : 1 + k + (step - 1) * k * k;
-    if (j < nf) {
-        const TbPart *rp = rows + ((size_t)b * S + win.first + step) * segs;
-        const TbPart *cp = parts + ((size_t)b * k + j) * chunks;
-        const int nparts = segs + chunks;
-        const int ncand = nparts * k;
-        const TbSlot sl = fr->slot[j];
-        const int f = sl.node;
-        // every load of this node is issued before any is used
-        float pm = -__builtin_huge_valf();
-        double ps = 0.0;
-        if (lane < nparts) {
-            const TbPart *pp = lane < segs ? rp + lane : cp + (lane - segs);
-            pm = pp->m;
-            ps = pp->s;
-        }
-        unsigned long long cand[kCandPerLane];
+    // Key i of part q (the rows', then the columns') belongs to lane
+    // (q kk + i) mod 64.
+    const int ksh = k <= 1 ? 0 : 32 - __builtin_clz(k - 1);
+    const size_t rp = ((size_t)b * S + win.first + step) * segs;
+    const int nkeys = nparts << ksh, rkeys = segs << ksh;
+    int nf = 0;
+    for (int j = wave; j < kTbMaxK; j += kTbWaves) {
+        if (j >= k && j >= kTbWaves) break;          // every wave runs the first round
+        const int jr = min(j, k - 1);                // slots past nf load stale data, unused
+        const size_t cp = ((size_t)b * k + jr) * chunks;
+        // unconditional loads, clamped (without hot tokens parts are never read)
+        const TbSum *ps1 = lane < segs || chunks == 0 ? rows.sum + rp + min(lane, segs - 1)
+                                                      : parts.sum + cp + (min(lane, nparts - 1) - segs);
+        float pm = ps1->m;
+        double ps = ps1->s;
+        unsigned long long cand[CPL];
+        int col[CPL];
         #pragma unroll
-        for (int u = 0; u < kCandPerLane; ++u) {
-            const int idx = lane + u * kWave;
-            unsigned long long key = 0ull;
-            if (idx < ncand) {
-                const int q = idx / k, r = idx - q * k;
-                key = q < segs ? rp[q].key[r] : cp[q - segs].key[r];
-            }
-            cand[u] = key;
+        for (int u = 0; u < CPL; ++u) {
+            const int x = min(lane + u * kWave, nkeys - 1);
+            const unsigned long long *kp = x < rkeys ? rows.key + (rp << ksh) + x : parts.key + (cp << ksh) + (x - rkeys);
+            cand[u] = *kp;
+            col[u] = chunks > 0 ? parts.col[(cp << ksh) + max(x - rkeys, 0)] : -1;
         }
-        const double pj = sl.joint;
+        const TbSlot sl = fr->slot[jr];
+        const int count = fr->count;
+        if (j == wave) {
+            between();
+            __syncthreads();
+        }
+        nf = count;
+        if (j >= nf) continue;
+        pm = lane < nparts ? pm : kNegInf;
+        #pragma unroll
+        for (int u = 0; u < CPL; ++u) {
+            if (lane + u * kWave >= nkeys) cand[u] = 0ull;
+            if (lane + u * kWave < rkeys) col[u] = -1;
+        }
         const float m = wave_allmax(pm);
-        const double s = wave_allsum(pm == -__builtin_huge_valf() ? 0.0 : ps * exp((double)pm - (double)m));
-        // rank r's key goes to lane r; the children's probabilities are then
-        // computed by lanes 0..k-1 at once
-        unsigned long long mine = 0ull;
-        for (int r = 0; r < k; ++r) {
-            unsigned long long best = 0ull;
-            #pragma unroll
-            for (int u = 0; u < kCandPerLane; ++u) best = umax64(best, cand[u]);
-            best = wave_max64(best);
-            #pragma unroll
-            for (int u = 0; u < kCandPerLane; ++u) cand[u] = cand[u] == best ? 0ull : cand[u];
-            mine = lane == r ? best : mine;
-        }
-        if (lane < k) {
-            const size_t at = (size_t)b * max_nodes + base + j * k + lane;
-            double joint = 0.0;
-            int tok = -1;
-            if (mine != 0ull) {
-                tok = key_index(mine);
-                joint = pj * (exp((double)key_value(mine) - (double)m) / s);
+        const double s = wave_allsum(pm == kNegInf ? 0.0 : ps * exp_nonpos((double)pm - (double)m, tab));
+        unsigned long long lm = 0ull;
+        #pragma unroll
+        for (int u = 0; u < CPL; ++u) lm = umax64(lm, cand[u]);
+        const unsigned long long fl = umax64(wave_floor64(lm, k), 1ull);    // 0 is no key
+        int n = 0;
+        #pragma unroll
+        for (int u = 0; u < CPL; ++u) {
+            const bool pass = cand[u] >= fl;
+            const unsigned long long mask = __ballot(pass);
+            if (mask == 0ull) continue;              // wave-uniform
+            const int at = n + below(mask);
+            if (pass && at < kTbList) {
+                sh.list[wave][at] = cand[u];
+                sh.lcol[wave][at] = col[u];
             }
-            node_tok[at] = tok;
-            node_par[at] = f;
-            node_joint[at] = joint;
-            s_joint[j * k + lane] = joint;
-            s_tok[j * k + lane] = tok;
-            s_hot[j * k + lane] = hot_row(hot_index, tok, V, H);   // loaded now, used after the ranking
+            n += __popcll(mask);
         }
+        if (n > kTbList) {
+            // k rounds of the largest remaining key
+            wave_lds_sync();
+            for (int q = 0; q < k; ++q) {
+                unsigned long long best = 0ull;
+                #pragma unroll
+                for (int u = 0; u < CPL; ++u) best = umax64(best, cand[u]);
+                best = wave_max64(best);
+                #pragma unroll
+                for (int u = 0; u < CPL; ++u)
+                    if (best != 0ull && cand[u] == best) {
+                        sh.list[wave][q] = best;
+                        sh.lcol[wave][q] = col[u];
+                        cand[u] = 0ull;
+                    }
+                if (best == 0ull && lane == 0) sh.list[wave][q] = 0ull;
+            }
+            n = k;
+        }
+        wave_lds_sync();
+        list_winners(sh.list[wave], sh.lcol[wave], n, k, lane, false, nullptr, nullptr, sh.win[0][wave],
+                     sh.wcol[0][wave]);
+        if (lane < k) {                              // lane i: child i; a rank without a key has no token
+            const unsigned long long key = sh.win[0][wave][lane];
+            const double joint = key == 0ull ? 0.0 : sl.joint * (exp_nonpos((double)key_value(key) - (double)m, tab) / s);
+            sh.joint[j * k + lane] = joint;
+            sh.col[j * k + lane] = key == 0ull ? -1 : sh.wcol[0][wave][lane];
+            if (writer) {
+                const size_t at = (size_t)b * max_nodes + base + j * k + lane;
+                node_tok[at] = key == 0ull ? -1 : key_index(key);
+                node_par[at] = sl.node;
+                node_joint[at] = joint;
+            }
+        }
+        wave_lds_sync();                             // the list is free for the next node
     }
     __syncthreads();
     // next frontier: the k children of this step with the largest joint
@@ -599,106 +655,420 @@ __global__ __launch_bounds__(kTbMaxK * kWave) void tb_select_kernel(
     // workgroup's threads), then add their parts.
     const int nc = nf * k;
     int tpc = 16;
-    while (tpc > 1 && nc * tpc > kTbMaxK * kWave) tpc >>= 1;
+    while (tpc > 1 && nc * tpc > kTbThreads) tpc >>= 1;
     {
-        const int i = threadIdx.x / tpc, part = threadIdx.x % tpc;
+        const int i = tid / tpc, part = tid % tpc;
         int rank = 0;
         double ji = 0.0;
         if (i < nc) {
-            ji = s_joint[i];
+            ji = sh.joint[i];
             for (int q = part; q < nc; q += tpc) {
-                const double jq = s_joint[q];
+                const double jq = sh.joint[q];
                 rank += (jq > ji || (jq == ji && q < i)) ? 1 : 0;
             }
         }
         rank = group_sum(rank, tpc);
-        if (i < nc && part == 0 && rank < k)
-            fr->slot[rank] = TbSlot{base + i, s_tok[i], s_hot[i], 0, ji};
-    }
-    if (threadIdx.x == 0) fr->count = min(k, nc);
-}
-
-// One workgroup per sequence: keep the `budget` nodes of largest joint
-// probability (ties to the earlier node), in creation order, parents renumbered.
-__global__ __launch_bounds__(kPruneThreads) void tb_prune_kernel(
-    const int32_t *__restrict__ accept_len, int r, int S, int k, int budget, int max_nodes,
-    const int32_t *__restrict__ node_tok,
-    const int32_t *__restrict__ node_par, const double *__restrict__ node_joint,
-    int32_t *__restrict__ parent, int32_t *__restrict__ token, float *__restrict__ joint,
-    int32_t *__restrict__ num_nodes) {
-    __shared__ double s_j[kPruneSlots];
-    __shared__ short s_i[kPruneSlots];
-    __shared__ short s_new[kPruneSlots];
-    __shared__ int s_warp[kPruneThreads / kWave];
-    const int b = blockIdx.x, tid = threadIdx.x;
-    const size_t nb = (size_t)b * max_nodes;
-    const TbWindow win = tb_window(accept_len, b, S, r);
-    const int n = win.count < 0 ? 0 : win.count == 0 ? 1 : 1 + k + (win.count - 1) * k * k;
-    int P2 = 1;
-    while (P2 < n) P2 <<= 1;
-    for (int i = tid; i < P2; i += kPruneThreads) {
-        s_j[i] = i < n ? node_joint[nb + i] : -1.0;
-        s_i[i] = (short)i;
-    }
-    __syncthreads();
-    // bitonic sort: joint descending, index ascending
-    for (int size = 2; size <= P2; size <<= 1) {
-        for (int stride = size >> 1; stride > 0; stride >>= 1) {
-            for (int i = tid; i < P2; i += kPruneThreads) {
-                const int pr = i ^ stride;
-                if (pr > i) {
-                    const bool desc = (i & size) == 0;
-                    const double ja = s_j[i], jb = s_j[pr];
-                    const int ia = s_i[i], ib = s_i[pr];
-                    const bool a_first = ja > jb || (ja == jb && ia < ib);
-                    if (a_first != desc) {
-                        s_j[i] = jb; s_j[pr] = ja;
-                        s_i[i] = (short)ib; s_i[pr] = (short)ia;
-                    }
-                }
-            }
-            __syncthreads();
+        if (i < nc && part == 0 && rank < k) {
+            const TbSlot sl = {base + i, sh.col[i], ji};
+            sh.slot[rank] = sl;
+            if (writer) next->slot[rank] = sl;
         }
     }
-    // keep flags by creation index, then ranks in creation order
-    const int kept = min(budget, n);
-    for (int i = tid; i < kPruneSlots; i += kPruneThreads) s_new[i] = 0;
-    __syncthreads();
-    for (int i = tid; i < kept; i += kPruneThreads) s_new[s_i[i]] = 1;
-    __syncthreads();
-    // exclusive prefix count of the flags (n <= 4096: 4 per thread)
-    constexpr int kPer = kPruneSlots / kPruneThreads;
-    int f[kPer], run = 0;
-    #pragma unroll
-    for (int u = 0; u < kPer; ++u) { f[u] = s_new[tid * kPer + u]; run += f[u]; }
-    const int lane = tid & (kWave - 1), w = tid / kWave;
-    int incl = run;
-    #pragma unroll
-    for (int off = 1; off < kWave; off <<= 1) {
-        const int o = __shfl_up(incl, off);
-        if (lane >= off) incl += o;
+    if (tid == 0) {
+        sh.nf = min(k, nc);
+        if (writer) next->count = min(k, nc);
     }
-    if (lane == kWave - 1) s_warp[w] = incl;
     __syncthreads();
-    int before = incl - run;
-    for (int q = 0; q < w; ++q) before += s_warp[q];
+}
+
+// LDS of a step workgroup: one of its roles.
+template <int U>
+struct StepShared {
+    static constexpr int kCols = U * kWave;          // columns of one pass
+    SelShared sel;
+    double exp2[kExpTab];
+    float x[kCols];                                  // the chunk's logits and vocabulary ids
+    int id[kCols];
+    u16x8 t[kTbWaves][kCols / 8];                    // a wave's table row, by its lanes' columns
+};
+
+struct StepArgs {
+    const float *logits;
+    const uint16_t *table;
+    const int32_t *hot_vocab, *hot_index, *root_token, *accept_len;
+    TbParts rows, parts_in, parts_out;
+    const TbFrontier *fr_in;
+    TbFrontier *fr_out;
+    int32_t *node_tok, *node_par;
+    double *node_joint;
+    int r, S, V, H, k, kk, step, chunks, chunk_len, segs, seg_len, max_nodes;
+};
+
+// Step `step`, workgroups 0 .. B chunks - 1: the selection of the step before
+// (at step 0 the frontier is the root), then the expansion of the frontier on
+// one chunk of the hot columns, x = l_step[hot[c]] + table[row of the node's
+// token][c], one wave per frontier node, in passes of 64 U columns (one pass
+// unless there are more than 32 chunks of them). The chunk's logits are gathered
+// once for all nodes, while the selection runs. Workgroup (b, chunk 0) stores
+// what the selection found. parts and frontier are double buffered by the step's
+// parity: this launch reads the step before's while it writes its own.
+// The other B segs workgroups reduce this step's non-hot tokens (RU per thread).
+// Bound by the chain partials -> children -> table row -> columns; two workgroups
+// share a CU, so the second kind costs little beside the first.
+template <int CPL, int U, int RU>
+__global__ __launch_bounds__(kTbThreads, 4) void tb_step_kernel(StepArgs p) {
+    constexpr int kCols = StepShared<U>::kCols;
+    constexpr int kG = kCols / kTbThreads;           // columns gathered per thread
+    __shared__ union Sh {
+        __device__ Sh() {}
+        StepShared<U> step;
+        RowsShared rows;
+    } shared;
+    const int S = p.S, V = p.V, H = p.H, k = p.k, step = p.step, chunks = p.chunks;
+    const int nexp = (int)gridDim.x / (chunks + p.segs) * chunks;
+    if ((int)blockIdx.x >= nexp) {
+        const int x = blockIdx.x - nexp, rb = x / p.segs, seg = x % p.segs;
+        const TbWindow rw = tb_window(p.accept_len, rb, S, p.r);
+        if (step >= rw.count) return;
+        const size_t row = (size_t)rb * S + rw.first + step, at = row * p.segs + seg;
+        const int v0 = seg * p.seg_len;
+        reduce_row<RU>(shared.rows, p.logits + row * V, p.hot_index, V, H, k, p.kk, v0, min(V, v0 + p.seg_len),
+                       p.rows.sum + at, p.rows.key + at * p.kk);
+        return;
+    }
+    SelShared &sh = shared.step.sel;
+    double *const s_exp2 = shared.step.exp2;
+    float *const s_x = shared.step.x;
+    int *const s_id = shared.step.id;
+    const uint16_t *const table = p.table;
+    const int32_t *const hot_vocab = p.hot_vocab;
+    const int b = blockIdx.x / chunks, c = blockIdx.x % chunks, chunk_len = p.chunk_len;
+    const TbWindow win = tb_window(p.accept_len, b, S, p.r);
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+    if (step == 0 && c == 0 && tid == 0) {           // the root
+        const int t = p.root_token[b];
+        const size_t at = (size_t)b * p.max_nodes;
+        p.node_tok[at] = t;
+        p.node_par[at] = -1;
+        p.node_joint[at] = 1.0;
+        p.fr_out[b].count = win.count > 0 ? 1 : 0;
+        p.fr_out[b].slot[0] = TbSlot{0, hot_row(p.hot_index, t, V, H), 1.0};
+    }
+    const bool expand = step < win.count;
+    const bool select = step > 0 && step - 1 < win.count;
+    if (!expand && !(select && c == 0)) return;      // this sequence's tree is complete
+    const int c0 = c * chunk_len, c1 = min(H, c0 + chunk_len);
+    // (the last row stands in where there is nothing to expand)
+    const float *l = p.logits + ((size_t)b * S + min(win.first + step, S - 1)) * V;
+    int id[kG];
+    float gx[kG];
+    // Loads only: indices are clamped and what lies outside becomes -inf when
+    // the columns are staged, so nothing waits here.
+    auto load_ids = [&](int p0) {
+        #pragma unroll
+        for (int g = 0; g < kG; ++g) id[g] = hot_vocab[min(p0 + tid + g * kTbThreads, c1 - 1)];
+    };
+    auto gather = [&]() {
+        #pragma unroll
+        for (int g = 0; g < kG; ++g) gx[g] = l[(unsigned)id[g] < (unsigned)V ? id[g] : 0];
+    };
+    load_ids(c0);
+    if (select) {
+        select_step<CPL>(sh, p.rows, p.segs, p.parts_in, chunks, win, b, S, k, step - 1, p.max_nodes,
+                         p.fr_in + b, p.fr_out + b, c == 0, s_exp2, p.node_tok, p.node_par, p.node_joint,
+                         [&] {
+                             gather();
+                             fill_exp2_table(s_exp2);
+                         });
+        if (!expand) return;
+    } else {
+        const int h = tid == 0 ? hot_row(p.hot_index, p.root_token[b], V, H) : -1;
+        gather();
+        fill_exp2_table(s_exp2);
+        if (tid == 0) {
+            sh.nf = 1;
+            sh.slot[0] = TbSlot{0, h, 1.0};
+        }
+        __syncthreads();
+    }
+    const int nf = sh.nf;
+    const bool aligned = (H & 7) == 0 && (c0 & 7) == 0 && (reinterpret_cast<uintptr_t>(table) & 15) == 0;
+    for (int j0 = 0; j0 < nf; j0 += kTbWaves) {      // one round for k <= 8
+        const int j = j0 + wave;
+        const int h = j < nf ? sh.slot[j].h : -1;
+        const uint16_t *trow = table + (size_t)max(h, 0) * H;
+        float M = kNegInf;
+        double sum = 0.0;
+        int cur = 0;                                 // which of sel.win holds the passes so far
+        if (lane < kTbMaxK) sh.win[0][wave][lane] = 0ull;
+        for (int p0 = c0; p0 < c1; p0 += kCols) {
+            // lane's columns: p0 + 512 q + 8 lane + e
+            u16x8 tv[U / 8];
+            if (j < nf && h >= 0) {
+                if (aligned && c1 - p0 >= kCols) {
+                    #pragma unroll
+                    for (int q = 0; q < U / 8; ++q)
+                        tv[q] = *reinterpret_cast<const u16x8 *>(trow + p0 + q * 512 + lane * 8);
+                } else {
+                    #pragma unroll
+                    for (int q = 0; q < U / 8; ++q)
+                        #pragma unroll
+                        for (int e = 0; e < 8; ++e) tv[q][e] = trow[min(p0 + q * 512 + lane * 8 + e, c1 - 1)];
+                }
+            } else {
+                #pragma unroll
+                for (int q = 0; q < U / 8; ++q) tv[q] = u16x8{0, 0, 0, 0, 0, 0, 0, 0};
+            }
+            if (j0 > 0 || p0 > c0) {                 // the first pass was gathered before
+                if (p0 > c0 || c1 - c0 > kCols) {
+                    load_ids(p0);
+                    gather();
+                }
+                __syncthreads();                     // every wave is done with the previous pass
+            }
+            #pragma unroll
+            for (int g = 0; g < kG; ++g) {
+                const bool use = (unsigned)id[g] < (unsigned)V && p0 + tid + g * kTbThreads < c1;
+                s_x[tid + g * kTbThreads] = use ? gx[g] : kNegInf;
+                s_id[tid + g * kTbThreads] = id[g];
+            }
+            __syncthreads();
+            if (j >= nf) continue;
+            float xv[U];
+            #pragma unroll
+            for (int q = 0; q < U / 8; ++q) {
+                const f32x4 a = *reinterpret_cast<const f32x4 *>(s_x + q * 512 + lane * 8);
+                const f32x4 d = *reinterpret_cast<const f32x4 *>(s_x + q * 512 + lane * 8 + 4);
+                #pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const float x = e < 4 ? a[e] : d[e - 4];
+                    xv[q * 8 + e] = h >= 0 ? x + __uint_as_float((unsigned)tv[q][e] << 16) : x;
+                }
+            }
+            float lm = kNegInf;
+            #pragma unroll
+            for (int u = 0; u < U; ++u) lm = fmaxf(lm, xv[u]);
+            const float pm = wave_allmax(lm);
+            const bool more = p0 > c0;
+            if (pm == kNegInf) continue;             // wave-uniform: no candidate
+            const float fl = fmaxf(wave_floor(lm, k), -__FLT_MAX__);     // -inf is no candidate
+            unsigned bits = 0u;
+            #pragma unroll
+            for (int u = 0; u < U; ++u) bits |= xv[u] >= fl ? 1u << u : 0u;
+            #pragma unroll
+            for (int q = 0; q < U / 8; ++q) shared.step.t[wave][q * kWave + lane] = tv[q];
+            // value of the pass's column cl, from LDS
+            auto value_at = [&](int cl) {
+                const unsigned t = reinterpret_cast<const uint16_t *>(shared.step.t[wave])[cl];
+                return h >= 0 ? s_x[cl] + __uint_as_float(t << 16) : s_x[cl];
+            };
+            int n = 0;
+            for (unsigned long long mask; (mask = __ballot(bits != 0u)) != 0ull && n <= kTbList;) {
+                const int at = n + below(mask);
+                if (bits != 0u && at < kTbList) sh.lcol[wave][at] = (__builtin_ctz(bits) << 6) | lane;
+                bits &= bits - 1u;
+                n += __popcll(mask);
+            }
+            if (n > kTbList) {
+                // k rounds of the largest key below the previous one
+                unsigned long long prev = ~0ull;
+                wave_lds_sync();
+                for (int i = 0; i < k; ++i) {
+                    unsigned long long best = 0ull;
+                    int bc = 0;
+                    #pragma unroll 1
+                    for (int cl = lane; cl < kCols; cl += kWave) {
+                        const float x = value_at(cl);
+                        const unsigned long long key = pack_key(order_key(x), (unsigned)s_id[cl]);
+                        if (x != kNegInf && key < prev && key > best) {
+                            best = key;
+                            bc = cl;
+                        }
+                    }
+                    prev = wave_max64(best);
+                    if (best == prev && best != 0ull) {
+                        sh.list[wave][i] = best;
+                        sh.lcol[wave][i] = p0 + bc;
+                    }
+                    if (prev == 0ull && lane == 0) {
+                        sh.list[wave][i] = 0ull;
+                        sh.lcol[wave][i] = 0;
+                    }
+                }
+                n = k;
+                wave_lds_sync();
+            } else {
+                wave_lds_sync();                     // the listed entries become keys
+                for (int i = lane; i < n; i += kWave) {
+                    const int e = sh.lcol[wave][i], u = e >> 6;
+                    const int cl = (u >> 3) * 512 + (e & (kWave - 1)) * 8 + (u & 7);
+                    sh.list[wave][i] = pack_key(order_key(value_at(cl)), (unsigned)s_id[cl]);
+                    sh.lcol[wave][i] = p0 + cl;
+                }
+            }
+            double ps = 0.0;
+            #pragma unroll
+            for (int u = 0; u < U; ++u) ps += exp_nonpos((double)xv[u] - (double)pm, s_exp2);
+            ps = wave_allsum(ps);
+            wave_lds_sync();
+            list_winners(sh.list[wave], sh.lcol[wave], n, k, lane, more, sh.win[cur][wave], sh.wcol[cur][wave],
+                         sh.win[cur ^ 1][wave], sh.wcol[cur ^ 1][wave]);
+            cur ^= 1;
+            merge_sum(M, sum, pm, ps, s_exp2);
+        }
+        if (j < nf) {
+            const size_t at = ((size_t)b * k + j) * chunks + c;
+            if (lane < p.kk) {
+                p.parts_out.key[at * p.kk + lane] = sh.win[cur][wave][lane];
+                p.parts_out.col[at * p.kk + lane] = sh.wcol[cur][wave][lane];
+            }
+            if (lane == 0) {
+                p.parts_out.sum[at].s = sum;
+                p.parts_out.sum[at].m = M;
+            }
+        }
+    }
+}
+
+// The rows alone (no hot tokens): every (sequence, step), and the roots.
+template <int RU>
+__global__ __launch_bounds__(kTbThreads, 4) void tb_rows_kernel(StepArgs p) {
+    __shared__ RowsShared sh;
+    const int row = blockIdx.x, seg = blockIdx.y, b = row / p.S, step = row % p.S;
+    const TbWindow win = tb_window(p.accept_len, b, p.S, p.r);
+    if (seg == 0 && step == 0 && threadIdx.x == 0) {
+        const size_t at = (size_t)b * p.max_nodes;
+        p.node_tok[at] = p.root_token[b];
+        p.node_par[at] = -1;
+        p.node_joint[at] = 1.0;
+        p.fr_out[b].count = win.count > 0 ? 1 : 0;
+        p.fr_out[b].slot[0] = TbSlot{0, -1, 1.0};
+    }
+    if (step < win.first || step - win.first >= win.count) return;   // a row that no step uses
+    const size_t at = (size_t)row * p.segs + seg;
+    const int v0 = seg * p.seg_len;
+    reduce_row<RU>(sh, p.logits + (size_t)row * p.V, nullptr, p.V, 0, p.k, p.kk, v0, min(p.V, v0 + p.seg_len),
+                   p.rows.sum + at, p.rows.key + at * p.kk);
+}
+
+// One workgroup per sequence: the selections of steps from .. S - 1 (the last
+// one, or all of them without hot tokens, where a step's children come from the
+// row partials alone), then the `budget` nodes of largest joint probability
+// (ties to the earlier node), in creation order, parents renumbered. The
+// budget-th largest is found by a histogram over 1024 buckets of joint
+// probability (32 per octave): better buckets are kept whole, the nodes of the
+// bucket it falls in are ranked by counting.
+template <int CPL>
+__global__ __launch_bounds__(kTbThreads) void tb_finish_kernel(
+    TbParts rows, int segs, TbParts parts0, TbParts parts1, int chunks, const int32_t *__restrict__ accept_len, int r,
+    int S, int k, int from, int budget, int max_nodes, TbFrontier *fr0, TbFrontier *fr1,
+    int32_t *node_tok, int32_t *node_par, double *node_joint, int32_t *__restrict__ parent,
+    int32_t *__restrict__ token, float *__restrict__ joint, int32_t *__restrict__ num_nodes) {
+    __shared__ SelShared sh;
+    __shared__ double s_exp2[kExpTab];
+    __shared__ int s_hist[kBuckets];
+    __shared__ int s_warp[kTbWaves];
+    __shared__ short s_new[kPruneSlots];
+    __shared__ short s_mem[kPruneSlots];             // nodes of the threshold bucket
+    __shared__ int s_bucket, s_before, s_nmem;
+    const int b = blockIdx.x, tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+    const TbWindow win = tb_window(accept_len, b, S, r);
+    for (int i = tid; i < kBuckets; i += kTbThreads) s_hist[i] = 0;
+    if (tid == 0) s_nmem = 0;
+    for (int step = from; step < S && step < win.count; ++step)
+        select_step<CPL>(sh, rows, segs, (step & 1) ? parts1 : parts0, chunks, win, b, S, k, step, max_nodes,
+                         ((step & 1) ? fr1 : fr0) + b, ((step & 1) ? fr0 : fr1) + b, true, s_exp2, node_tok,
+                         node_par, node_joint, [&] { if (step == from) fill_exp2_table(s_exp2); });
+    const size_t nb = (size_t)b * max_nodes;
+    const int n = win.count < 0 ? 0 : win.count == 0 ? 1 : 1 + k + (win.count - 1) * k * k;
+    const int kept = min(budget, n);
+    constexpr int kPer = kPruneSlots / kTbThreads;   // consecutive nodes per thread
+    // bucket 0 holds 1.0; 32 buckets per halving, everything below 2^-32 in the last
+    auto bucket_of = [](double j) {
+        const unsigned hi = (unsigned)((unsigned long long)__double_as_longlong(j) >> 32);
+        return (int)min((0x3FF00000u - min(hi, 0x3FF00000u)) >> 15, (unsigned)(kBuckets - 1));
+    };
+    double jn[kPer];
+    const int i0 = tid * kPer;
     __syncthreads();
     #pragma unroll
-    for (int u = 0; u < kPer; ++u) {
-        const int i = tid * kPer + u;
-        s_new[i] = f[u] ? (short)before : (short)-1;
+    for (int u = 0; u < kPer; ++u) jn[u] = i0 + u < n ? node_joint[nb + i0 + u] : 0.0;
+    #pragma unroll
+    for (int u = 0; u < kPer; ++u)
+        if (i0 + u < n) atomicAdd(&s_hist[bucket_of(jn[u])], 1);
+    __syncthreads();
+    // inclusive prefix over the buckets, two per thread: the one holding the
+    // kept-th node
+    constexpr int kBpt = kBuckets / kTbThreads;
+    int f[kBpt], run = 0;
+    #pragma unroll
+    for (int u = 0; u < kBpt; ++u) { f[u] = s_hist[tid * kBpt + u]; run += f[u]; }
+    auto block_exclusive = [&](int total) {          // exclusive prefix of `total` over the threads
+        int incl = total;
+        #pragma unroll
+        for (int off = 1; off < kWave; off <<= 1) {
+            const int o = __shfl_up(incl, off);
+            if (lane >= off) incl += o;
+        }
+        if (lane == kWave - 1) s_warp[wave] = incl;
+        __syncthreads();
+        int before = incl - total;
+        for (int q = 0; q < wave; ++q) before += s_warp[q];
+        __syncthreads();
+        return before;
+    };
+    int before = block_exclusive(run);
+    #pragma unroll
+    for (int u = 0; u < kBpt; ++u) {
+        if (before < kept && before + f[u] >= kept) { s_bucket = tid * kBpt + u; s_before = before; }
         before += f[u];
     }
     __syncthreads();
-    for (int i = tid; i < n; i += kPruneThreads) {
-        const int ni = s_new[i];
-        if (ni < 0) continue;
-        const int pp = node_par[nb + i];
+    const int tb = kept > 0 ? s_bucket : -1, left = kept > 0 ? kept - s_before : 0;
+    #pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+        const int i = i0 + u;
+        if (i >= n) continue;
+        const int bk = bucket_of(jn[u]);
+        s_new[i] = bk < tb ? 1 : 0;
+        if (bk == tb) s_mem[atomicAdd(&s_nmem, 1)] = (short)i;
+    }
+    __syncthreads();
+    const int nm = s_nmem;
+    for (int x = tid; x < nm; x += kTbThreads) {
+        const int i = s_mem[x];
+        const double ji = node_joint[nb + i];
+        int rank = 0;
+        for (int q = 0; q < nm && rank < left; ++q) {
+            const int o = s_mem[q];
+            const double jo = node_joint[nb + o];
+            rank += (jo > ji || (jo == ji && o < i)) ? 1 : 0;
+        }
+        if (rank < left) s_new[i] = 1;
+    }
+    __syncthreads();
+    // ranks in creation order
+    int g[kPer];
+    run = 0;
+    #pragma unroll
+    for (int u = 0; u < kPer; ++u) { g[u] = i0 + u < n ? s_new[i0 + u] : 0; run += g[u]; }
+    before = block_exclusive(run);
+    #pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+        if (i0 + u < n) s_new[i0 + u] = g[u] ? (short)before : (short)-1;
+        before += g[u];
+    }
+    __syncthreads();
+    #pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+        const int i = i0 + u;
+        if (!g[u]) continue;
+        const int ni = s_new[i], pp = node_par[nb + i];
         parent[(size_t)b * budget + ni] = pp < 0 ? -1 : s_new[pp];
         token[(size_t)b * budget + ni] = node_tok[nb + i];
-        joint[(size_t)b * budget + ni] = (float)node_joint[nb + i];
+        joint[(size_t)b * budget + ni] = (float)jn[u];
     }
-    for (int i = kept + tid; i < budget; i += kPruneThreads) {
+    for (int i = kept + tid; i < budget; i += kTbThreads) {
         parent[(size_t)b * budget + i] = -1;
         token[(size_t)b * budget + i] = -1;
         joint[(size_t)b * budget + i] = 0.f;
@@ -706,32 +1076,51 @@ __global__ __launch_bounds__(kPruneThreads) void tb_prune_kernel(
     if (tid == 0) num_nodes[b] = kept;
 }
 
+// Workgroups that fill the chip.
+constexpr int kFill = 256;
+
 }  // namespace
 
 TreeBuildPlan tree_build_plan(int B, int S, int V, int H, int k) {
     TreeBuildPlan pl;
     const long rows = (long)B * S;
-    // at least 16384 tokens per workgroup (64 per thread), so that the top-k
-    // filter, not the insertions, sets the cost per token
-    long segs = ((long)V + 16383) / 16384;
-    if (segs > 32) segs = 32;
-    if (segs < 1) segs = 1;
+    // Tokens of a rows workgroup: 16 per thread, or 4 while that leaves CUs idle
+    // (and needs no more than 32 segments). Columns of a step workgroup: 32 per
+    // lane, or 16 likewise.
+    auto parts_of = [](long n, long per) {
+        const long x = (n + per - 1) / per;
+        return n <= 0 ? 0l : x > kMaxParts ? (long)kMaxParts : x;
+    };
+    pl.row_u = ((long)B * parts_of(V, 16 * kTbThreads) >= kFill / 2 || (long)V > 4l * kTbThreads * kMaxParts) ? 16 : 4;
+    const long segs = parts_of(V, (long)pl.row_u * kTbThreads);
     pl.segs = (int)segs;
     pl.seg_len = (int)(((long)V + segs - 1) / segs);
-    long chunks = 0;
-    if (H > 0) {
-        chunks = ((long)H + 2047) / 2048;            // at least 2048 columns per (one-wave) workgroup
-        if (chunks > 32) chunks = 32;
-        if (chunks < 1) chunks = 1;
-    }
+    pl.col_u = ((long)B * parts_of(H, 32 * kWave) >= kFill / 2 || (long)H > 16l * kWave * kMaxParts) ? 32 : 16;
+    const long chunks = parts_of(H, (long)pl.col_u * kWave);
     pl.chunks = (int)chunks;
-    pl.chunk_len = chunks > 0 ? (int)(((long)H + chunks - 1) / chunks) : 0;
+    // a multiple of 8 columns, for the wide table loads
+    pl.chunk_len = chunks > 0 ? (int)((((long)H + chunks - 1) / chunks + 7) / 8 * 8) : 0;
     pl.max_nodes = 1 + k + (S - 1) * k * k;
-    pl.rows_bytes = (size_t)rows * segs * sizeof(TbPart);
-    pl.hot_logits_bytes = (size_t)rows * H * sizeof(float);
-    pl.parts_bytes = (size_t)B * k * (chunks > 0 ? chunks : 1) * sizeof(TbPart);
-    pl.nodes_bytes = (size_t)B * pl.max_nodes * (2 * sizeof(int32_t) + sizeof(double));
+    pl.kk = k <= 1 ? 1 : k <= 2 ? 2 : k <= 4 ? 4 : k <= 8 ? 8 : 16;
+    // workspace: as many parts as any split of these sizes has, so that it does
+    // not grow for a smaller call
+    pl.row_parts = (size_t)rows * parts_of(V, 4 * kTbThreads);
+    pl.col_parts = (size_t)B * k * parts_of(H, 16 * kWave);
     pl.frontier_bytes = (size_t)B * sizeof(TbFrontier);
+    pl.bytes = 256;
+    auto add = [&](size_t bytes) { pl.bytes += (bytes + 255) & ~(size_t)255; };
+    add(pl.row_parts * sizeof(TbSum));
+    add(pl.row_parts * pl.kk * sizeof(unsigned long long));
+    for (int i = 0; i < 2; ++i) {
+        add(pl.col_parts * sizeof(TbSum));
+        add(pl.col_parts * pl.kk * sizeof(unsigned long long));
+        add(pl.col_parts * pl.kk * sizeof(int32_t));
+        add(pl.frontier_bytes);
+    }
+    const size_t nn = (size_t)B * pl.max_nodes;
+    add(nn * sizeof(int32_t));
+    add(nn * sizeof(int32_t));
+    add(nn * sizeof(double));
     return pl;
 }
 
@@ -749,39 +1138,56 @@ hipError_t launch_tree_build(const float *logits, const int32_t *root_token,
         base += (bytes + 255) & ~(size_t)255;
         return p;
     };
-    TbPart *rows = reinterpret_cast<TbPart *>(carve(pl.rows_bytes));
-    TbPart *parts = reinterpret_cast<TbPart *>(carve(pl.parts_bytes));
-    float *hot_logits = reinterpret_cast<float *>(carve(pl.hot_logits_bytes));
+    auto carve_parts = [&](size_t parts, bool cols) {
+        TbParts t;
+        t.sum = reinterpret_cast<TbSum *>(carve(parts * sizeof(TbSum)));
+        t.key = reinterpret_cast<unsigned long long *>(carve(parts * pl.kk * sizeof(unsigned long long)));
+        t.col = cols ? reinterpret_cast<int *>(carve(parts * pl.kk * sizeof(int32_t))) : nullptr;
+        return t;
+    };
+    const TbParts rows = carve_parts(pl.row_parts, false);
+    TbParts parts[2];
+    TbFrontier *frontier[2];
+    for (auto &t : parts) t = carve_parts(pl.col_parts, true);
     const size_t nn = (size_t)B * pl.max_nodes;
     int32_t *node_tok = reinterpret_cast<int32_t *>(carve(nn * sizeof(int32_t)));
     int32_t *node_par = reinterpret_cast<int32_t *>(carve(nn * sizeof(int32_t)));
     double *node_joint = reinterpret_cast<double *>(carve(nn * sizeof(double)));
-    TbFrontier *frontier = reinterpret_cast<TbFrontier *>(carve(pl.frontier_bytes));
+    for (auto &f : frontier) f = reinterpret_cast<TbFrontier *>(carve(pl.frontier_bytes));
 
-    hipError_t e = launch_kernel(tb_rows_kernel, dim3(B * S, pl.segs), dim3(kTbThreads), s, logits,
-                                 hot_vocab, hot_index, root_token, accept_len, r, S, V, H, k,
-                                 pl.seg_len, rows, hot_logits, pl.max_nodes, node_tok, node_par,
-                                 node_joint, frontier);
-    for (int i = 0; i < S && e == hipSuccess; ++i) {
-        if (pl.chunks > 0)
-            e = launch_kernel(tb_expand_kernel, dim3(B, k, pl.chunks), dim3(kExpThreads), s,
-                              hot_logits, table, hot_vocab, accept_len, r, S, V, H, k, i,
-                              pl.chunk_len, (const TbFrontier *)frontier, parts);
-        if (e == hipSuccess) {
-            // candidate keys per lane of the selection: (segs + chunks) k of them
-            const int ncand = (pl.segs + pl.chunks) * k;
-            auto sel = ncand <= 2 * kWave ? tb_select_kernel<2>
-                       : ncand <= 4 * kWave ? tb_select_kernel<4>
-                       : ncand <= 8 * kWave ? tb_select_kernel<8> : tb_select_kernel<16>;
-            e = launch_kernel(sel, dim3(B), dim3(kTbMaxK * kWave), s, rows, pl.segs, parts,
-                              pl.chunks, accept_len, hot_index, r, S, V, H, k, i, pl.max_nodes,
-                              node_tok, node_par, node_joint, frontier);
+    // candidate keys per lane of a selection: (segs + chunks) parts of kk keys
+    const int per_lane = ((pl.segs + pl.chunks) * pl.kk + kWave - 1) / kWave;
+    StepArgs a{logits, table, hot_vocab, hot_index, root_token, accept_len, rows, parts[1], parts[0],
+               frontier[1], frontier[0], node_tok, node_par, node_joint, r, S, V, H, k, pl.kk, 0,
+               pl.chunks, pl.chunk_len, pl.segs, pl.seg_len, pl.max_nodes};
+    hipError_t e = hipSuccess;
+    if (pl.chunks == 0) {
+        e = launch_kernel(pl.row_u == 16 ? tb_rows_kernel<16> : tb_rows_kernel<4>, dim3(B * S, pl.segs),
+                          dim3(kTbThreads), s, a);
+    }
+    if (pl.chunks > 0) {
+        auto pick = [&](auto cpl) {
+            constexpr int C = decltype(cpl)::value;
+            return pl.col_u == 32 ? (pl.row_u == 16 ? tb_step_kernel<C, 32, 16> : tb_step_kernel<C, 32, 4>)
+                                  : (pl.row_u == 16 ? tb_step_kernel<C, 16, 16> : tb_step_kernel<C, 16, 4>);
+        };
+        auto sk = per_lane <= 4   ? pick(std::integral_constant<int, 4>())
+                  : per_lane <= 8 ? pick(std::integral_constant<int, 8>())
+                                  : pick(std::integral_constant<int, 16>());
+        for (int i = 0; i < S && e == hipSuccess; ++i) {
+            a.step = i;
+            a.parts_in = parts[(i + 1) & 1];
+            a.parts_out = parts[i & 1];
+            a.fr_in = frontier[(i + 1) & 1];
+            a.fr_out = frontier[i & 1];
+            e = launch_kernel(sk, dim3(B * (pl.chunks + pl.segs)), dim3(kTbThreads), s, a);
         }
     }
     if (e == hipSuccess)
-        e = launch_kernel(tb_prune_kernel, dim3(B), dim3(kPruneThreads), s, accept_len, r, S, k,
-                          budget, pl.max_nodes, node_tok, node_par, node_joint, parent, token,
-                          joint, num_nodes);
+        e = launch_kernel(per_lane <= 4 ? tb_finish_kernel<4> : per_lane <= 8 ? tb_finish_kernel<8> : tb_finish_kernel<16>, dim3(B), dim3(kTbThreads), s,
+                          rows, pl.segs, parts[0], parts[1], pl.chunks, accept_len, r, S, k,
+                          pl.chunks > 0 ? S - 1 : 0, budget, pl.max_nodes, frontier[0], frontier[1],
+                          node_tok, node_par, node_joint, parent, token, joint, num_nodes);
     return e;
 }
 

@@ -344,12 +344,7 @@ static bool tree_build_shape_ok(int B, int S, int V, int H, int k) {
 
 size_t tv_tree_build_workspace_size(int B, int S, int V, int H, int k) {
     if (!tree_build_shape_ok(B, S, V, H, k)) return 0;
-    const tv::TreeBuildPlan pl = tv::tree_build_plan(B, S, V, H, k);
-    const size_t nn = (size_t)B * pl.max_nodes;
-    return round_up(pl.rows_bytes, 256) + round_up(pl.parts_bytes, 256) +
-           round_up(pl.hot_logits_bytes, 256) +
-           2 * round_up(nn * sizeof(int32_t), 256) + round_up(nn * sizeof(double), 256) +
-           round_up(pl.frontier_bytes, 256) + 256;
+    return tv::tree_build_plan(B, S, V, H, k).bytes;
 }
 
 int tree_build(const float *logits, const int32_t *root_token, const uint16_t *token_info,

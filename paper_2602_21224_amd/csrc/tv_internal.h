@@ -44,12 +44,17 @@ __device__ __forceinline__ unsigned long long pack_key(unsigned int key, unsigne
     return ((unsigned long long)key << 32) | (unsigned long long)(0xFFFFFFFFu - idx);
 }
 
-// Launch geometry and workspace layout of the tree builder.
+// Launch geometry and workspace layout of the tree builder. parts and frontier
+// are carved twice (double buffered over the steps).
 struct TreeBuildPlan {
     int segs, seg_len;         // vocabulary segments per (sequence, step) row
-    int chunks, chunk_len;     // hot-column chunks per frontier node (0 without hot tokens)
+    int row_u;                 // tokens per thread and pass of the rows kernel
+    int chunks, chunk_len;     // hot-column chunks per sequence (0 without hot tokens)
+    int col_u;                 // columns per lane and pass of the step kernel
     int max_nodes;             // nodes of the unpruned tree: 1 + k + (S - 1) k^2
-    size_t rows_bytes, parts_bytes, hot_logits_bytes, nodes_bytes, frontier_bytes;
+    int kk;                    // keys per part: the power of two at or above k
+    size_t row_parts, col_parts, frontier_bytes;
+    size_t bytes;              // of the whole workspace
 };
 TreeBuildPlan tree_build_plan(int B, int S, int V, int H, int k);
 

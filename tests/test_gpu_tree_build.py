@@ -65,6 +65,73 @@ def test_tree_build_cases(oracle_mod, case):
     compare(oracle_mod, T, x, f"case{case}")
 
 
+SPLITS = [
+    # (B, S, V, H, k, budget): edges of the builder's splits
+    (1, 2, 300000, 50, 3, 12),          # rows of more than one pass per segment
+    (1, 2, 8200, 1025, 9, 40),          # two segments and two chunks, both nearly empty; k above 8
+    (17, 2, 8193, 2056, 8, 30),         # two unequal chunks, wide table loads in one of them
+    (9, 3, 70000, 32769, 10, 60),       # 17 chunks of 32 columns per lane, rows not aligned
+    (3, 3, 4000, 4000, 16, 200),        # all hot, 16 branches: two rounds of nodes per wave
+    (16, 2, 40000, 20001, 5, 20),       # odd hot count
+]
+
+
+@pytest.mark.parametrize("case", range(len(SPLITS)))
+def test_tree_build_splits(oracle_mod, case):
+    T = U.require_gpu()
+    B, S, V, H, k, budget = SPLITS[case]
+    x = W.make_tree_build_inputs(f"s{case}", 130 + case, B=B, S=S, V=V, H=H, k=k, budget=budget)
+    compare(oracle_mod, T, x, f"split{case}")
+
+
+def test_tree_build_columns_in_passes(oracle_mod):
+    """More hot tokens than 32 chunks of one pass hold (65536): every chunk runs
+    in two passes whose winners and sums are merged. All table rows are the same
+    row, so that the oracle needs only one of them."""
+    T = U.require_gpu()
+    B, S, V, H, k, budget = 1, 3, 70000, 66001, 4, 30
+    print(f"case passes: V={V} H={H}", flush=True)
+    x = W.make_tree_build_inputs("p", 140, B=B, S=S, V=V, H=64, k=k, budget=budget)
+    rng = np.random.default_rng(1)
+    hot = rng.permutation(V)[:H].astype(np.int32)
+    index = np.full(V, -1, np.int32)
+    index[hot] = np.arange(H, dtype=np.int32)
+    row = W.f32_to_bf16_bits(rng.standard_normal(H, dtype=np.float32))
+    margins = []
+    want = oracle_mod.tree_build(x.logits, x.root, np.broadcast_to(row, (H, H)), hot, k, budget, margins)
+    assert min(margins) > 1e-9
+    tab = U.dev(row.view(np.int16)).view(torch.bfloat16).expand(H, H).contiguous()
+    par, tok, jnt, nn = T.tree_build(U.dev(x.logits), U.dev(x.root), tab, U.dev(hot), U.dev(index),
+                                     k=k, budget=budget)
+    torch.cuda.synchronize()
+    np.testing.assert_array_equal(tok.cpu().numpy(), want[1])
+    np.testing.assert_array_equal(par.cpu().numpy(), want[0])
+    np.testing.assert_allclose(jnt.cpu().numpy(), want[2], rtol=1e-6)
+
+
+@pytest.mark.parametrize("H,k", [(0, 3), (3000, 8), (5000, 16), (3000, 11)])
+def test_tree_build_equal_logits(H, k):
+    """Every candidate ties: more than any candidate list holds, and the k lowest
+    vocabulary ids win, with probability 1 / V each."""
+    T = U.require_gpu()
+    V, B, S = 5000, 2, 1
+    rng = np.random.default_rng(H + k)
+    hot = rng.permutation(V)[:H].astype(np.int32)
+    index = np.full(V, -1, np.int32)
+    index[hot] = np.arange(H, dtype=np.int32)
+    logits = torch.full((B, S, V), -0.75, device="cuda")
+    tab = torch.zeros((H, H), dtype=torch.bfloat16, device="cuda") if H else None
+    roots = np.array([7, 4999], np.int32)
+    par, tok, jnt, nn = T.tree_build(logits, U.dev(roots), tab, U.dev(hot) if H else None,
+                                     U.dev(index) if H else None, k=k, budget=k + 1)
+    torch.cuda.synchronize()
+    for b in range(B):
+        assert tok[b].tolist() == [int(roots[b])] + list(range(k))
+        assert par[b].tolist() == [-1] + [0] * k
+    np.testing.assert_allclose(jnt.cpu().numpy()[:, 1:], 1.0 / V, rtol=1e-6)
+    assert (nn.cpu().numpy() == k + 1).all()
+
+
 def test_tree_build_narrative(oracle_mod):
     """The worked example of §5.2 (golden fixture) on the GPU."""
     T = U.require_gpu()
