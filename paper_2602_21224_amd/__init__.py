@@ -15,5 +15,6 @@ __all__ = ["tree_verify_attention", "tree_argmax_accept", "tree_argmax_accept_no
 def __getattr__(name):
     if name in __all__:
         from . import _lib
-        return getattr(_lib, name)
+        value = globals()[name] = getattr(_lib, name)      # found directly from now on
+        return value
     raise AttributeError(name)
