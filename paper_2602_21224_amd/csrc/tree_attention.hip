@@ -880,8 +880,18 @@ __global__ __launch_bounds__(NW * kWave) void tree_attention_kernel(AttnParams p
     const int nw = min(p.num_wg, total);
     auto share_start = [&](int u) { return (int)(((long long)min(u, nw) * total) / max(nw, 1)); };
     auto share_of = [&](int t) { return (int)(((long long)(t + 1) * nw - 1) / total); };
-    const int start = share_start(w);
-    const int end = share_start(w + 1);
+    int start = share_start(w), end = share_start(w + 1);
+    if (p.whole_units) {
+        // workgroup w takes unit w whole (unit order: sequence, KV head, row
+        // block; a sequence with fewer row blocks leaves workgroups idle)
+        const int rbs = row_blocks_of(p.N * p.G, p);
+        const int wb = w / (p.Hkv * rbs), wg = w / rbs % p.Hkv, wr = w % rbs;
+        const int rows = g_nn[wb] * p.G, ntp = (g_len[wb] + KT - 1) / KT;
+        start = g_cum[wb] + wg * tiles_per_head(ntp, rows, p);
+        for (int x = 0; x < min(wr, row_blocks_of(rows, p)); ++x)
+            start += p.setup_tiles + ntp + tree_tiles_of_block(x, rows, p);
+        end = wr < row_blocks_of(rows, p) ? start + p.setup_tiles + ntp + tree_tiles_of_block(wr, rows, p) : start;
+    }
     const unsigned ring_base = lds_addr(g_ring);
     Issue ld;
     ld.init(wave_u, lane, p);
@@ -1407,7 +1417,7 @@ hipError_t launch_dn(const AttnParams &p, hipStream_t s) {
             ? launch_kernel(tree_attention_kernel<D, NW, true, false>, dim3(p.num_wg), dim3(NW * kWave), s, p)
             : launch_kernel(tree_attention_kernel<D, NW, false, false>, dim3(p.num_wg), dim3(NW * kWave), s, p);
     if (e != hipSuccess) return e;
-    if (p.num_wg > 1) {
+    if (p.num_wg > 1 && !p.whole_units) {
         constexpr int kRowsPerWg = 256 / (D / 8);
         const int chunks = (p.rows_per_block + kRowsPerWg - 1) / kRowsPerWg;
         const int stride = (p.num_wg + kNumXcd - 1) / kNumXcd * kNumXcd;

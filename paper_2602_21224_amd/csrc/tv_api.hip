@@ -203,6 +203,16 @@ int tree_verify_attention(const uint16_t *q, const uint16_t *k_tree, const uint1
     long num_wg = est / kMinShareTiles;
     if (num_wg < 1) num_wg = 1;
     if (num_wg > max_wg) num_wg = max_wg;
+    // Short units are not worth splitting: one workgroup per unit saves the merge
+    // launch and the partials it reads, 3-4 us, for about 1.2 us per tile of a
+    // unit of at most 16 rows or of head size 64, and 2 us of the others. Measured
+    // (us per call, whole and split): 16 rows of 64, 4 tiles 10.5 and 12.6; 12 rows
+    // of 128, 4 tiles 13.0 and 14.2; 132 rows of 128, 3 tiles 14.5 and 16.4; 256
+    // rows, 3 tiles 14.9 and 15.0, 4 tiles 16.9 and 15.0.
+    const long units = (long)B * Hkv * s.row_blocks;
+    const long unit_tiles = (hint_len + tv::kKeyTile - 1) / tv::kKeyTile + (N + tv::kKeyTile - 1) / tv::kKeyTile;
+    const bool whole = units <= max_wg && unit_tiles <= (s.rows <= 16 || D == 64 ? 4 : 3);
+    if (whole) num_wg = units;
 
     tv::AttnParams p;
     p.q = q; p.k_tree = k_tree; p.v_tree = v_tree; p.k_cache = k_cache; p.v_cache = v_cache;
@@ -220,6 +230,7 @@ int tree_verify_attention(const uint16_t *q, const uint16_t *k_tree, const uint1
     p.small_pages = P < 1024 / (2 * D) ? 1 : 0;
     p.narrow = s.rows <= 16 ? 1 : 0;
     p.num_wg = (int)num_wg;
+    p.whole_units = whole ? 1 : 0;
     const float sc = scale > 0.f ? scale : 1.0f / sqrtf((float)D);
     p.scale = sc;
     p.scale_log2 = sc * 1.4426950408889634f;

@@ -58,6 +58,10 @@ struct TreeBuildPlan {
 };
 TreeBuildPlan tree_build_plan(int B, int S, int V, int H, int k);
 
+// The builder for more than 8 branches (tree_build_many.hip).
+bool tree_build_many(int k);
+size_t tree_build_many_bytes(int B, int S, int V, int H, int k);
+
 // Launch parameters of the tree-attention kernels (all sizes in elements).
 struct AttnParams {
     const uint16_t *q, *k_tree, *v_tree, *k_cache, *v_cache;
@@ -74,6 +78,7 @@ struct AttnParams {
     int narrow;                  // units of at most 16 rows: tiles shared out over the waves
     int setup_tiles;             // cost of starting a unit piece, in tiles (work balance)
     int num_wg;
+    int whole_units;             // every workgroup takes one unit whole (nothing to merge)
     float scale_log2;            // softmax scale * log2(e)
     float scale;                 // softmax scale
 };
@@ -111,6 +116,12 @@ hipError_t launch_tree_build(const float *logits, const int32_t *root_token,
                              int S, int V, int H, int k, int budget, int32_t *parent,
                              int32_t *token, float *joint, int32_t *num_nodes, void *workspace,
                              hipStream_t s);
+hipError_t launch_tree_build_many(const float *logits, const int32_t *root_token,
+                                  const uint16_t *table, const int32_t *hot_vocab,
+                                  const int32_t *hot_index, const int32_t *accept_len, int r,
+                                  int B, int S, int V, int H, int k, int budget, int32_t *parent,
+                                  int32_t *token, float *joint, int32_t *num_nodes,
+                                  void *workspace, hipStream_t s);
 hipError_t launch_tree_attention(const AttnParams &p, int head_dim, int waves, hipStream_t s);
 hipError_t launch_argmax_accept(const float *logits, const int32_t *draft, const int32_t *parent,
                                 const int32_t *num_nodes, int B, int N, int V, int segs,

@@ -71,6 +71,33 @@ def test_small_shapes_all_outputs(oracle_mod, case):
     full_compare(oracle_mod, T, w, f"small{case}")
 
 
+@pytest.mark.parametrize("B,N,Hq,Hkv,D,L,nodes,hint", [
+    (3, 16, 8, 8, 64, (0, 192), None, None),          # up to the longest units taken whole
+    (2, 12, 32, 32, 128, (193, 256), None, None),     # just past them: split
+    (2, 80, 32, 8, 128, (0, 64), [80, 7], None),      # two row blocks, one in the second sequence
+    (3, 70, 16, 2, 128, (1, 64), [0, 70, 33], None),  # three row blocks, an empty sequence
+    (2, 20, 8, 2, 128, (500, 900), None, 10),         # understated lengths: whole, though long
+])
+def test_units_taken_whole(oracle_mod, B, N, Hq, Hkv, D, L, nodes, hint):
+    """Short units run one per workgroup without a merge; the bound of the lengths
+    decides it and never changes a result."""
+    T = U.require_gpu()
+    it = iter(nodes) if nodes else None
+    w = W.make_workload("whole", 90 + N, B=B, N=N, Hq=Hq, Hkv=Hkv, D=D, kv_len=L, V=64, poison=True,
+                        parent_fn=lambda r: W.tree_random_depth_capped(r, N, 6)[:next(it) if it else N],
+                        with_logits=False)
+    if hint is None:
+        full_compare(oracle_mod, T, w, "whole")
+        return
+    d = U.upload(w)
+    got, lse = T.tree_verify_attention(d["q"], d["k_tree"], d["v_tree"], d["k_cache"], d["v_cache"],
+                                       d["page_table"], d["kv_len"], d["parent"], max_kv_len=hint)
+    torch.cuda.synchronize()
+    want, wlse = oracle_mod.tree_attention(w.q, w.k_tree, w.v_tree, w.k_cache, w.v_cache, w.page_table,
+                                           w.kv_len, w.parent)
+    U.assert_attention_close(U.bf16_to_f64(got), want, lse.cpu().numpy().astype(np.float64), wlse, "whole")
+
+
 def test_explicit_scale(oracle_mod):
     T = U.require_gpu()
     w = wl(7, B=2, N=20, Hq=8, Hkv=2, D=128, L=(40, 90), tree="capped")
