@@ -163,8 +163,9 @@ CALL_KERNELS = {
     "tree_verify_attention": ("tree_attention_kernel", "tree_attention_merge_kernel"),
     "tree_argmax_accept": ("argmax_segments_kernel", "accept_kernel"),
     "kv_compact_accepted": ("kv_compact_kernel",),
-    "tree_build": ("tb_rows_kernel", "tb_expand_kernel", "tb_select_kernel", "tb_prune_kernel"),
-    "tree_lm_head_argmax_accept": ("lm_keys_clear_kernel", "lm_head_argmax_kernel", "accept_kernel"),
+    "tree_build": ("tb_finish_kernel", "tb_step_kernel", "tb_rows_kernel"),
+    "tree_lm_head_argmax_accept": ("lm_keys_clear_kernel", "lm_head_argmax_kernel",
+                                   "lm_head_stream_kernel", "accept_kernel"),
 }
 
 

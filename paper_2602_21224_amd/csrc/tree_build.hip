@@ -27,8 +27,7 @@
 //
 // Top-k of a set held in registers: the maxima of k or more disjoint groups of
 // it are k candidates, so none of the k largest lies below the smallest of
-// those maxima. The entries at or above that floor (about 22 for 8 groups, 54
-// for 16) are listed in LDS and ranked by counting; a list that would overflow
+// those maxima. The entries at or above that floor (about 22) are listed in LDS and ranked by counting; a list that would overflow
 // (many equal entries) is replaced by k rounds of a plain maximum. The list holds
 // 256 entries: of 2048 random ones, fewer than one set in a million has more at
 // or above its floor. (With 64, one wave in 700 did, and its rounds set the time
@@ -40,10 +39,12 @@
 // 22 us, 19 without its rows, which took 43 us of their own for the seven steps.
 #include "tv_internal.h"
 
+#include <algorithm>
+
 namespace tv {
 namespace {
 
-constexpr int kTbThreads = 512;
+constexpr int kTbThreads = 512;            // 8 waves: one per frontier node (k <= 8)
 constexpr int kTbWaves = kTbThreads / kWave;
 constexpr int kTbList = 4 * kWave;         // listed candidates of one wave
 constexpr int kRowsList = 512;      // listed candidates of a rows workgroup
@@ -197,26 +198,24 @@ __device__ __forceinline__ unsigned long long dpp64u(unsigned long long v) {
     return ((unsigned long long)dpp32<C>((unsigned int)(v >> 32)) << 32) | dpp32<C>((unsigned int)v);
 }
 
-// Smallest of the maxima of 8 groups of 8 lanes (k <= 8) or 16 groups of 4:
-// at least k of the lanes' values are at or above it.
-__device__ __forceinline__ float wave_floor(float v, int k) {
+// Smallest of the maxima of 8 groups of 8 lanes: at least 8 (>= k) of the lanes'
+// values are at or above it.
+__device__ __forceinline__ float wave_floor(float v) {
     const auto mx = [](float a, unsigned b) { return fmaxf(a, __uint_as_float(b)); };
     const auto mn = [](float a, unsigned b) { return fminf(a, __uint_as_float(b)); };
     v = mx(v, dpp32<kDppXor1>(__float_as_uint(v)));
     v = mx(v, dpp32<kDppXor2>(__float_as_uint(v)));
-    const unsigned hm = dpp32<kDppHalfMirror>(__float_as_uint(v));
-    v = k <= 8 ? mx(v, hm) : mn(v, hm);
+    v = mx(v, dpp32<kDppHalfMirror>(__float_as_uint(v)));
     v = mn(v, dpp32<kDppMirror>(__float_as_uint(v)));
     const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
     v = mn(__uint_as_float(r[0]), r[1]);
     const auto h = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
     return mn(__uint_as_float(h[0]), h[1]);
 }
-__device__ __forceinline__ unsigned long long wave_floor64(unsigned long long v, int k) {
+__device__ __forceinline__ unsigned long long wave_floor64(unsigned long long v) {
     v = umax64(v, dpp64u<kDppXor1>(v));
     v = umax64(v, dpp64u<kDppXor2>(v));
-    const unsigned long long hm = dpp64u<kDppHalfMirror>(v);
-    v = k <= 8 ? umax64(v, hm) : umin64(v, hm);
+    v = umax64(v, dpp64u<kDppHalfMirror>(v));
     v = umin64(v, dpp64u<kDppMirror>(v));
     #pragma unroll
     for (int half = 0; half < 2; ++half) {
@@ -383,7 +382,7 @@ __device__ __forceinline__ TbWindow tb_window(const int32_t *accept_len, int b, 
 // LDS of a rows reduction.
 struct RowsShared {
     double exp2[kExpTab];
-    float gm[2 * kTbWaves];                          // group maxima: waves, or half waves
+    float gm[kTbWaves];                              // the waves' maxima: 8 groups
     double sum[kTbWaves];
     unsigned long long list[kRowsList], best[kTbWaves], win[kTbMaxK];
     int n;
@@ -429,24 +428,12 @@ __device__ __forceinline__ void reduce_row(RowsShared &sh, const float *__restri
         for (int u = 0; u < U; ++u) m = fmaxf(m, xv[u]);
         __syncthreads();                             // the previous pass's lists are done with
         if (tid == 0) s_n = 0;
-        {
-            // group maxima: the waves' for k <= 8, their halves' above
-            m = fmaxf(m, __uint_as_float(dpp32<kDppXor1>(__float_as_uint(m))));
-            m = fmaxf(m, __uint_as_float(dpp32<kDppXor2>(__float_as_uint(m))));
-            m = fmaxf(m, __uint_as_float(dpp32<kDppHalfMirror>(__float_as_uint(m))));
-            m = fmaxf(m, __uint_as_float(dpp32<kDppMirror>(__float_as_uint(m))));
-            const auto x = __builtin_amdgcn_permlane16_swap(__float_as_uint(m), __float_as_uint(m), false, false);
-            m = fmaxf(__uint_as_float(x[0]), __uint_as_float(x[1]));
-            if (k <= 8) {
-                const auto h = __builtin_amdgcn_permlane32_swap(__float_as_uint(m), __float_as_uint(m), false, false);
-                m = fmaxf(__uint_as_float(h[0]), __uint_as_float(h[1]));
-            }
-            if ((lane & 31) == 0) s_gm[wave * 2 + (lane >> 5)] = m;
-        }
+        m = wave_allmax(m);
+        if (lane == 0) s_gm[wave] = m;
         __syncthreads();
         float pm = kNegInf, fl = -kNegInf;
         #pragma unroll
-        for (int g = 0; g < 2 * kTbWaves; ++g) {
+        for (int g = 0; g < kTbWaves; ++g) {
             pm = fmaxf(pm, s_gm[g]);
             fl = fminf(fl, s_gm[g]);
         }
@@ -560,9 +547,8 @@ __device__ __forceinline__ void select_step(SelShared &sh, TbParts rows, int seg
     const size_t rp = ((size_t)b * S + win.first + step) * segs;
     const int nkeys = nparts << ksh, rkeys = segs << ksh;
     int nf = 0;
-    for (int j = wave; j < kTbMaxK; j += kTbWaves) {
-        if (j >= k && j >= kTbWaves) break;          // every wave runs the first round
-        const int jr = min(j, k - 1);                // slots past nf load stale data, unused
+    {
+        const int j = wave, jr = min(j, k - 1);      // slots past nf load stale data, unused
         const size_t cp = ((size_t)b * k + jr) * chunks;
         // unconditional loads, clamped (without hot tokens parts are never read)
         const TbSum *ps1 = lane < segs || chunks == 0 ? rows.sum + rp + min(lane, segs - 1)
@@ -580,72 +566,70 @@ __device__ __forceinline__ void select_step(SelShared &sh, TbParts rows, int seg
         }
         const TbSlot sl = fr->slot[jr];
         const int count = fr->count;
-        if (j == wave) {
-            between();
-            __syncthreads();
-        }
+        between();
+        __syncthreads();
         nf = count;
-        if (j >= nf) continue;
-        pm = lane < nparts ? pm : kNegInf;
-        #pragma unroll
-        for (int u = 0; u < CPL; ++u) {
-            if (lane + u * kWave >= nkeys) cand[u] = 0ull;
-            if (lane + u * kWave < rkeys) col[u] = -1;
-        }
-        const float m = wave_allmax(pm);
-        const double s = wave_allsum(pm == kNegInf ? 0.0 : ps * exp_nonpos((double)pm - (double)m, tab));
-        unsigned long long lm = 0ull;
-        #pragma unroll
-        for (int u = 0; u < CPL; ++u) lm = umax64(lm, cand[u]);
-        const unsigned long long fl = umax64(wave_floor64(lm, k), 1ull);    // 0 is no key
-        int n = 0;
-        #pragma unroll
-        for (int u = 0; u < CPL; ++u) {
-            const bool pass = cand[u] >= fl;
-            const unsigned long long mask = __ballot(pass);
-            if (mask == 0ull) continue;              // wave-uniform
-            const int at = n + below(mask);
-            if (pass && at < kTbList) {
-                sh.list[wave][at] = cand[u];
-                sh.lcol[wave][at] = col[u];
+        if (j < nf) {
+            pm = lane < nparts ? pm : kNegInf;
+            #pragma unroll
+            for (int u = 0; u < CPL; ++u) {
+                if (lane + u * kWave >= nkeys) cand[u] = 0ull;
+                if (lane + u * kWave < rkeys) col[u] = -1;
             }
-            n += __popcll(mask);
-        }
-        if (n > kTbList) {
-            // k rounds of the largest remaining key
+            const float m = wave_allmax(pm);
+            const double s = wave_allsum(pm == kNegInf ? 0.0 : ps * exp_nonpos((double)pm - (double)m, tab));
+            unsigned long long lm = 0ull;
+            #pragma unroll
+            for (int u = 0; u < CPL; ++u) lm = umax64(lm, cand[u]);
+            const unsigned long long fl = umax64(wave_floor64(lm), 1ull);    // 0 is no key
+            int n = 0;
+            #pragma unroll
+            for (int u = 0; u < CPL; ++u) {
+                const bool pass = cand[u] >= fl;
+                const unsigned long long mask = __ballot(pass);
+                if (mask == 0ull) continue;              // wave-uniform
+                const int at = n + below(mask);
+                if (pass && at < kTbList) {
+                    sh.list[wave][at] = cand[u];
+                    sh.lcol[wave][at] = col[u];
+                }
+                n += __popcll(mask);
+            }
+            if (n > kTbList) {
+                // k rounds of the largest remaining key
+                wave_lds_sync();
+                for (int q = 0; q < k; ++q) {
+                    unsigned long long best = 0ull;
+                    #pragma unroll
+                    for (int u = 0; u < CPL; ++u) best = umax64(best, cand[u]);
+                    best = wave_max64(best);
+                    #pragma unroll
+                    for (int u = 0; u < CPL; ++u)
+                        if (best != 0ull && cand[u] == best) {
+                            sh.list[wave][q] = best;
+                            sh.lcol[wave][q] = col[u];
+                            cand[u] = 0ull;
+                        }
+                    if (best == 0ull && lane == 0) sh.list[wave][q] = 0ull;
+                }
+                n = k;
+            }
             wave_lds_sync();
-            for (int q = 0; q < k; ++q) {
-                unsigned long long best = 0ull;
-                #pragma unroll
-                for (int u = 0; u < CPL; ++u) best = umax64(best, cand[u]);
-                best = wave_max64(best);
-                #pragma unroll
-                for (int u = 0; u < CPL; ++u)
-                    if (best != 0ull && cand[u] == best) {
-                        sh.list[wave][q] = best;
-                        sh.lcol[wave][q] = col[u];
-                        cand[u] = 0ull;
-                    }
-                if (best == 0ull && lane == 0) sh.list[wave][q] = 0ull;
-            }
-            n = k;
-        }
-        wave_lds_sync();
-        list_winners(sh.list[wave], sh.lcol[wave], n, k, lane, false, nullptr, nullptr, sh.win[0][wave],
-                     sh.wcol[0][wave]);
-        if (lane < k) {                              // lane i: child i; a rank without a key has no token
-            const unsigned long long key = sh.win[0][wave][lane];
-            const double joint = key == 0ull ? 0.0 : sl.joint * (exp_nonpos((double)key_value(key) - (double)m, tab) / s);
-            sh.joint[j * k + lane] = joint;
-            sh.col[j * k + lane] = key == 0ull ? -1 : sh.wcol[0][wave][lane];
-            if (writer) {
-                const size_t at = (size_t)b * max_nodes + base + j * k + lane;
-                node_tok[at] = key == 0ull ? -1 : key_index(key);
-                node_par[at] = sl.node;
-                node_joint[at] = joint;
+            list_winners(sh.list[wave], sh.lcol[wave], n, k, lane, false, nullptr, nullptr, sh.win[0][wave],
+                         sh.wcol[0][wave]);
+            if (lane < k) {                              // lane i: child i; a rank without a key has no token
+                const unsigned long long key = sh.win[0][wave][lane];
+                const double joint = key == 0ull ? 0.0 : sl.joint * (exp_nonpos((double)key_value(key) - (double)m, tab) / s);
+                sh.joint[j * k + lane] = joint;
+                sh.col[j * k + lane] = key == 0ull ? -1 : sh.wcol[0][wave][lane];
+                if (writer) {
+                    const size_t at = (size_t)b * max_nodes + base + j * k + lane;
+                    node_tok[at] = key == 0ull ? -1 : key_index(key);
+                    node_par[at] = sl.node;
+                    node_joint[at] = joint;
+                }
             }
         }
-        wave_lds_sync();                             // the list is free for the next node
     }
     __syncthreads();
     // next frontier: the k children of this step with the largest joint
@@ -716,7 +700,7 @@ struct StepArgs {
 // Bound by the chain partials -> children -> table row -> columns; two workgroups
 // share a CU, so the second kind costs little beside the first.
 template <int CPL, int U, int RU>
-__global__ __launch_bounds__(kTbThreads, 4) void tb_step_kernel(StepArgs p) {
+__global__ __launch_bounds__(kTbThreads, CPL > 4 ? 2 : 4) void tb_step_kernel(StepArgs p) {
     constexpr int kCols = StepShared<U>::kCols;
     constexpr int kG = kCols / kTbThreads;           // columns gathered per thread
     __shared__ union Sh {
@@ -793,8 +777,8 @@ __global__ __launch_bounds__(kTbThreads, 4) void tb_step_kernel(StepArgs p) {
     }
     const int nf = sh.nf;
     const bool aligned = (H & 7) == 0 && (c0 & 7) == 0 && (reinterpret_cast<uintptr_t>(table) & 15) == 0;
-    for (int j0 = 0; j0 < nf; j0 += kTbWaves) {      // one round for k <= 8
-        const int j = j0 + wave;
+    {
+        const int j = wave;                          // k <= 8 here
         const int h = j < nf ? sh.slot[j].h : -1;
         const uint16_t *trow = table + (size_t)max(h, 0) * H;
         float M = kNegInf;
@@ -805,10 +789,10 @@ __global__ __launch_bounds__(kTbThreads, 4) void tb_step_kernel(StepArgs p) {
             // lane's columns: p0 + 512 q + 8 lane + e
             u16x8 tv[U / 8];
             if (j < nf && h >= 0) {
-                if (aligned && c1 - p0 >= kCols) {
+                if (aligned) {                       // what lies past the chunk is not used
                     #pragma unroll
                     for (int q = 0; q < U / 8; ++q)
-                        tv[q] = *reinterpret_cast<const u16x8 *>(trow + p0 + q * 512 + lane * 8);
+                        tv[q] = *reinterpret_cast<const u16x8 *>(trow + min(p0 + q * 512 + lane * 8, H - 8));
                 } else {
                     #pragma unroll
                     for (int q = 0; q < U / 8; ++q)
@@ -819,11 +803,9 @@ __global__ __launch_bounds__(kTbThreads, 4) void tb_step_kernel(StepArgs p) {
                 #pragma unroll
                 for (int q = 0; q < U / 8; ++q) tv[q] = u16x8{0, 0, 0, 0, 0, 0, 0, 0};
             }
-            if (j0 > 0 || p0 > c0) {                 // the first pass was gathered before
-                if (p0 > c0 || c1 - c0 > kCols) {
-                    load_ids(p0);
-                    gather();
-                }
+            if (p0 > c0) {                           // the first pass was gathered before
+                load_ids(p0);
+                gather();
                 __syncthreads();                     // every wave is done with the previous pass
             }
             #pragma unroll
@@ -851,7 +833,7 @@ __global__ __launch_bounds__(kTbThreads, 4) void tb_step_kernel(StepArgs p) {
             const float pm = wave_allmax(lm);
             const bool more = p0 > c0;
             if (pm == kNegInf) continue;             // wave-uniform: no candidate
-            const float fl = fmaxf(wave_floor(lm, k), -__FLT_MAX__);     // -inf is no candidate
+            const float fl = fmaxf(wave_floor(lm), -__FLT_MAX__);     // -inf is no candidate
             unsigned bits = 0u;
             #pragma unroll
             for (int u = 0; u < U; ++u) bits |= xv[u] >= fl ? 1u << u : 0u;
@@ -969,7 +951,8 @@ __global__ __launch_bounds__(kTbThreads) void tb_finish_kernel(
     __shared__ int s_hist[kBuckets];
     __shared__ int s_warp[kTbWaves];
     __shared__ short s_new[kPruneSlots];
-    __shared__ short s_mem[kPruneSlots];             // nodes of the threshold bucket
+    __shared__ short s_mem[kPruneSlots];             // nodes of the threshold bucket,
+    __shared__ double s_mj[kPruneSlots];             // their joint probabilities
     __shared__ int s_bucket, s_before, s_nmem;
     const int b = blockIdx.x, tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
     const TbWindow win = tb_window(accept_len, b, S, r);
@@ -1031,18 +1014,21 @@ __global__ __launch_bounds__(kTbThreads) void tb_finish_kernel(
         if (i >= n) continue;
         const int bk = bucket_of(jn[u]);
         s_new[i] = bk < tb ? 1 : 0;
-        if (bk == tb) s_mem[atomicAdd(&s_nmem, 1)] = (short)i;
+        if (bk == tb) {
+            const int at = atomicAdd(&s_nmem, 1);
+            s_mem[at] = (short)i;
+            s_mj[at] = jn[u];
+        }
     }
     __syncthreads();
     const int nm = s_nmem;
     for (int x = tid; x < nm; x += kTbThreads) {
         const int i = s_mem[x];
-        const double ji = node_joint[nb + i];
+        const double ji = s_mj[x];
         int rank = 0;
         for (int q = 0; q < nm && rank < left; ++q) {
-            const int o = s_mem[q];
-            const double jo = node_joint[nb + o];
-            rank += (jo > ji || (jo == ji && o < i)) ? 1 : 0;
+            const double jo = s_mj[q];
+            rank += (jo > ji || (jo == ji && s_mem[q] < i)) ? 1 : 0;
         }
         if (rank < left) s_new[i] = 1;
     }
@@ -1091,17 +1077,26 @@ TreeBuildPlan tree_build_plan(int B, int S, int V, int H, int k) {
         const long x = (n + per - 1) / per;
         return n <= 0 ? 0l : x > kMaxParts ? (long)kMaxParts : x;
     };
-    pl.row_u = ((long)B * parts_of(V, 16 * kTbThreads) >= kFill / 2 || (long)V > 4l * kTbThreads * kMaxParts) ? 16 : 4;
+    // Small ones only while a selection's keys stay 4 per lane (its instance with
+    // 8 leaves room for one workgroup per CU).
+    pl.kk = k <= 1 ? 1 : k <= 2 ? 2 : k <= 4 ? 4 : 8;
+    const bool small_r = (long)B * parts_of(V, 16 * kTbThreads) < kFill / 2 && (long)V <= 4l * kTbThreads * kMaxParts;
+    const bool small_c = (long)B * parts_of(H, 32 * kWave) < kFill / 2 && (long)H <= 16l * kWave * kMaxParts;
+    auto keys = [&](bool sr, bool sc) {
+        return (parts_of(V, (sr ? 4 : 16) * kTbThreads) + parts_of(H, (sc ? 16 : 32) * kWave)) * pl.kk;
+    };
+    const bool sr = small_r && keys(true, false) <= 4 * kWave;
+    const bool sc = small_c && keys(sr, true) <= 4 * kWave;
+    pl.row_u = sr ? 4 : 16;
+    pl.col_u = sc ? 16 : 32;
     const long segs = parts_of(V, (long)pl.row_u * kTbThreads);
     pl.segs = (int)segs;
     pl.seg_len = (int)(((long)V + segs - 1) / segs);
-    pl.col_u = ((long)B * parts_of(H, 32 * kWave) >= kFill / 2 || (long)H > 16l * kWave * kMaxParts) ? 32 : 16;
     const long chunks = parts_of(H, (long)pl.col_u * kWave);
     pl.chunks = (int)chunks;
     // a multiple of 8 columns, for the wide table loads
     pl.chunk_len = chunks > 0 ? (int)((((long)H + chunks - 1) / chunks + 7) / 8 * 8) : 0;
     pl.max_nodes = 1 + k + (S - 1) * k * k;
-    pl.kk = k <= 1 ? 1 : k <= 2 ? 2 : k <= 4 ? 4 : k <= 8 ? 8 : 16;
     // workspace: as many parts as any split of these sizes has, so that it does
     // not grow for a smaller call
     pl.row_parts = (size_t)rows * parts_of(V, 4 * kTbThreads);
@@ -1121,6 +1116,7 @@ TreeBuildPlan tree_build_plan(int B, int S, int V, int H, int k) {
     add(nn * sizeof(int32_t));
     add(nn * sizeof(int32_t));
     add(nn * sizeof(double));
+    if (tree_build_many(k)) pl.bytes = std::max(pl.bytes, tree_build_many_bytes(B, S, V, H, k));
     return pl;
 }
 
@@ -1131,6 +1127,14 @@ hipError_t launch_tree_build(const float *logits, const int32_t *root_token,
                              int32_t *token, float *joint, int32_t *num_nodes, void *workspace,
                              hipStream_t s) {
     if (B == 0) return hipSuccess;
+    // One wave per frontier node and one launch per step up to 8 branches. With
+    // more, nodes and selection would take two rounds per wave, and launches of
+    // their own win (tree_build_many.hip): k 10, 16 sequences 297 against 231 us, 4
+    // sequences of 32000 tokens 137 against 133, one without hot tokens 134 against
+    // 89; k 8, 16 sequences 158 against 199.
+    if (tree_build_many(k))
+        return launch_tree_build_many(logits, root_token, table, hot_vocab, hot_index, accept_len, r, B, S, V, H, k,
+                                      budget, parent, token, joint, num_nodes, workspace, s);
     const TreeBuildPlan pl = tree_build_plan(B, S, V, H, k);
     char *base = static_cast<char *>(workspace);
     auto carve = [&](size_t bytes) {
@@ -1171,9 +1175,7 @@ hipError_t launch_tree_build(const float *logits, const int32_t *root_token,
             return pl.col_u == 32 ? (pl.row_u == 16 ? tb_step_kernel<C, 32, 16> : tb_step_kernel<C, 32, 4>)
                                   : (pl.row_u == 16 ? tb_step_kernel<C, 16, 16> : tb_step_kernel<C, 16, 4>);
         };
-        auto sk = per_lane <= 4   ? pick(std::integral_constant<int, 4>())
-                  : per_lane <= 8 ? pick(std::integral_constant<int, 8>())
-                                  : pick(std::integral_constant<int, 16>());
+        auto sk = per_lane <= 4 ? pick(std::integral_constant<int, 4>()) : pick(std::integral_constant<int, 8>());
         for (int i = 0; i < S && e == hipSuccess; ++i) {
             a.step = i;
             a.parts_in = parts[(i + 1) & 1];
@@ -1184,7 +1186,7 @@ hipError_t launch_tree_build(const float *logits, const int32_t *root_token,
         }
     }
     if (e == hipSuccess)
-        e = launch_kernel(per_lane <= 4 ? tb_finish_kernel<4> : per_lane <= 8 ? tb_finish_kernel<8> : tb_finish_kernel<16>, dim3(B), dim3(kTbThreads), s,
+        e = launch_kernel(per_lane <= 4 ? tb_finish_kernel<4> : tb_finish_kernel<8>, dim3(B), dim3(kTbThreads), s,
                           rows, pl.segs, parts[0], parts[1], pl.chunks, accept_len, r, S, k,
                           pl.chunks > 0 ? S - 1 : 0, budget, pl.max_nodes, frontier[0], frontier[1],
                           node_tok, node_par, node_joint, parent, token, joint, num_nodes);
