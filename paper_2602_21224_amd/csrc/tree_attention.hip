@@ -854,7 +854,7 @@ __device__ __forceinline__ void narrow_tile(NarrowState<D> &st, unsigned kbase, 
     }
 }
 
-template <int D, int NW, bool SMALL, bool NARROW>
+template <int D, int NW, bool SMALL, bool NARROW, bool WHOLE>
 __global__ __launch_bounds__(NW * kWave) void tree_attention_kernel(AttnParams p) {
     using Gm = Geo<D>;
     using Issue = TileIssue<D, NW, SMALL>;
@@ -881,7 +881,7 @@ __global__ __launch_bounds__(NW * kWave) void tree_attention_kernel(AttnParams p
     auto share_start = [&](int u) { return (int)(((long long)min(u, nw) * total) / max(nw, 1)); };
     auto share_of = [&](int t) { return (int)(((long long)(t + 1) * nw - 1) / total); };
     int start = share_start(w), end = share_start(w + 1);
-    if (p.whole_units) {
+    if constexpr (WHOLE) {
         // workgroup w takes unit w whole (unit order: sequence, KV head, row
         // block; a sequence with fewer row blocks leaves workgroups idle)
         const int rbs = row_blocks_of(p.N * p.G, p);
@@ -1400,22 +1400,26 @@ __global__ __launch_bounds__(256) void tree_attention_merge_kernel(AttnParams p,
         p.lse[((size_t)b * p.N + node) * p.Hq + hq] = (M + __builtin_amdgcn_logf(den)) * kLn2;
 }
 
+// Units taken whole have instances of their own, so that the split ones keep their
+// code: with the choice inside the kernel it came out up to 0.8 % slower (45 nodes of
+// head size 64 over 300-2500 keys 21.1 -> 21.3 us).
+template <int D, int NW, bool NARROW>
+hipError_t launch_main(const AttnParams &p, hipStream_t s) {
+    auto go = [&](auto kernel) { return launch_kernel(kernel, dim3(p.num_wg), dim3(NW * kWave), s, p); };
+    if (p.whole_units)
+        return p.small_pages ? go(tree_attention_kernel<D, NW, true, NARROW, true>)
+                             : go(tree_attention_kernel<D, NW, false, NARROW, true>);
+    return p.small_pages ? go(tree_attention_kernel<D, NW, true, NARROW, false>)
+                         : go(tree_attention_kernel<D, NW, false, NARROW, false>);
+}
+
 template <int D, int NW>
 hipError_t launch_dn(const AttnParams &p, hipStream_t s) {
     hipError_t e;
-    bool narrow_done = false;
-    if constexpr (NW == 4) {
-        if (p.narrow) {
-            e = p.small_pages
-                ? launch_kernel(tree_attention_kernel<D, NW, true, true>, dim3(p.num_wg), dim3(NW * kWave), s, p)
-                : launch_kernel(tree_attention_kernel<D, NW, false, true>, dim3(p.num_wg), dim3(NW * kWave), s, p);
-            narrow_done = true;
-        }
-    }
-    if (!narrow_done)
-        e = p.small_pages
-            ? launch_kernel(tree_attention_kernel<D, NW, true, false>, dim3(p.num_wg), dim3(NW * kWave), s, p)
-            : launch_kernel(tree_attention_kernel<D, NW, false, false>, dim3(p.num_wg), dim3(NW * kWave), s, p);
+    if constexpr (NW == 4)
+        e = p.narrow ? launch_main<D, NW, true>(p, s) : launch_main<D, NW, false>(p, s);
+    else
+        e = launch_main<D, NW, false>(p, s);
     if (e != hipSuccess) return e;
     if (p.num_wg > 1 && !p.whole_units) {
         constexpr int kRowsPerWg = 256 / (D / 8);

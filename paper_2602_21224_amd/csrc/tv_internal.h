@@ -78,9 +78,9 @@ struct AttnParams {
     int narrow;                  // units of at most 16 rows: tiles shared out over the waves
     int setup_tiles;             // cost of starting a unit piece, in tiles (work balance)
     int num_wg;
-    int whole_units;             // every workgroup takes one unit whole (nothing to merge)
     float scale_log2;            // softmax scale * log2(e)
     float scale;                 // softmax scale
+    int whole_units;             // every workgroup takes one unit whole (nothing to merge)
 };
 
 // Workgroup -> logical index remap: the hardware hands consecutive workgroup
