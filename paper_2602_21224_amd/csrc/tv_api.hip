@@ -408,7 +408,7 @@ static bool lm_head_shape_ok(int B, int N, int V, int d) {
         return false;
     const long long rblocks = ((long long)B * N + 255) / 256;
     const long long groups = ((long long)tv::lm_head_vocab_tiles(V) + 7) / 8 * 8 * rblocks;
-    return groups <= 0x7FFFFFFFll;
+    return groups <= 0x7FFFFFFFll - 256;         // a workgroup's next tile (256 further on) fits an int
 }
 
 size_t tv_lm_head_workspace_size(int B, int N, int V, int d) {

@@ -183,3 +183,11 @@ def test_lm_head_argument_checks(lib):
     need = lib.tv_lm_head_workspace_size(2, 64, 1000, 256)
     assert need >= 2 * 64 * 8 and lm(ws_bytes=need - 1) == -4
     assert lib.tv_lm_head_workspace_size(2, 64, 1000, 40) == 0
+
+
+def test_lm_head_tile_steps_fit_an_int(lib):
+    # a workgroup steps from tile to tile by up to 256: the last 256 counts below
+    # 2^31 are refused (18705 row blocks x 114808 vocabulary tiles = 2^31 - 8)
+    size = lambda B, V: lib.tv_lm_head_workspace_size(B, 256, V, 64)
+    assert size(18705, 114808 * 256) == 0
+    assert size(18704, 114808 * 256) > 0
