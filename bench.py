@@ -390,7 +390,7 @@ def run_tree_build(args, T, torch):
                      "unit": "GB/s", "frac": round(ach / HBM_PEAK_GBS, 4),
                      "traffic": load_traffic("tree_build", args.workload), "kernel": "tree_build",
                      "avg_us": round(t_call.mean() * 1e6, 2), "algorithmic_bytes": int(nbytes),
-                     "launches_per_call": 2 * x.S + 2},
+                     "launches_per_call": (2 if x.H == 0 else x.S + 1) if x.k <= 8 else 2 * x.S + 2},
         "call_us_p10_p50_p90": [pct(t_call, 10), pct(t_call, 50), pct(t_call, 90)],
         "warmup_steps_run": warm_steps,
         "timed_steps_with_events": len(sampled),
