@@ -646,9 +646,10 @@ __device__ __forceinline__ void select_step(SelShared &sh, TbParts rows, int seg
         double ji = 0.0;
         if (i < nc) {
             ji = sh.joint[i];
+            const long long ki = joint_key(ji);
             for (int q = part; q < nc; q += tpc) {
-                const double jq = sh.joint[q];
-                rank += (jq > ji || (jq == ji && q < i)) ? 1 : 0;
+                const long long kq = joint_key(sh.joint[q]);
+                rank += (kq > ki || (kq == ki && q < i)) ? 1 : 0;
             }
         }
         rank = group_sum(rank, tpc);
@@ -952,7 +953,7 @@ __global__ __launch_bounds__(kTbThreads) void tb_finish_kernel(
     __shared__ int s_warp[kTbWaves];
     __shared__ short s_new[kPruneSlots];
     __shared__ short s_mem[kPruneSlots];             // nodes of the threshold bucket,
-    __shared__ double s_mj[kPruneSlots];             // their joint probabilities
+    __shared__ long long s_mj[kPruneSlots];          // their joint probabilities' keys
     __shared__ int s_bucket, s_before, s_nmem;
     const int b = blockIdx.x, tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
     const TbWindow win = tb_window(accept_len, b, S, r);
@@ -1017,18 +1018,18 @@ __global__ __launch_bounds__(kTbThreads) void tb_finish_kernel(
         if (bk == tb) {
             const int at = atomicAdd(&s_nmem, 1);
             s_mem[at] = (short)i;
-            s_mj[at] = jn[u];
+            s_mj[at] = joint_key(jn[u]);
         }
     }
     __syncthreads();
     const int nm = s_nmem;
     for (int x = tid; x < nm; x += kTbThreads) {
         const int i = s_mem[x];
-        const double ji = s_mj[x];
+        const long long ki = s_mj[x];
         int rank = 0;
         for (int q = 0; q < nm && rank < left; ++q) {
-            const double jo = s_mj[q];
-            rank += (jo > ji || (jo == ji && s_mem[q] < i)) ? 1 : 0;
+            const long long kq = s_mj[q];
+            rank += (kq > ki || (kq == ki && s_mem[q] < i)) ? 1 : 0;
         }
         if (rank < left) s_new[i] = 1;
     }

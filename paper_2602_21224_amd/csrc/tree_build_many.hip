@@ -597,9 +597,10 @@ __global__ __launch_bounds__(kTbMaxK * kWave) void tb_select_kernel(
         double ji = 0.0;
         if (i < nc) {
             ji = s_joint[i];
+            const long long ki = joint_key(ji);
             for (int q = part; q < nc; q += tpc) {
-                const double jq = s_joint[q];
-                rank += (jq > ji || (jq == ji && q < i)) ? 1 : 0;
+                const long long kq = joint_key(s_joint[q]);
+                rank += (kq > ki || (kq == ki && q < i)) ? 1 : 0;
             }
         }
         rank = group_sum(rank, tpc);

@@ -248,6 +248,45 @@ def test_tree_build_workspace_alignment(oracle_mod):
     np.testing.assert_allclose(jnt.cpu().numpy(), want[2], rtol=1e-6, atol=0)
 
 
+@pytest.mark.parametrize("k", [4, 8, 12])
+@pytest.mark.parametrize("H", [0, 600])
+def test_tree_build_not_finite_stays_in_bounds(H, k):
+    """Logits and table entries that are not finite break the contract, so the
+    tree is unspecified, but NaN joint probabilities must not leave frontier slots
+    or kept nodes undefined: node counts and links stay valid, and nothing is
+    written outside the outputs."""
+    T = U.require_gpu()
+    B, S, V, budget, pad = 5, 4, 3000, 20, 64
+    print(f"case not finite H={H} k={k}", flush=True)
+    x = W.make_tree_build_inputs("nf", 150 + k, B=B, S=S, V=V, H=H, k=k, budget=budget)
+    logits = x.logits.copy()
+    rng = np.random.default_rng(k)
+    logits[0] = np.nan                                     # no candidate at all
+    logits[1][rng.random((S, V)) < 0.3] = np.nan
+    logits[2, :, rng.integers(0, V, 3)] = np.inf
+    logits[3] = -np.inf                                    # fewer candidates than branches, then infinities
+    logits[3, 0, 17] = 1.0
+    logits[3, 1:, :] = np.inf
+    tab = None
+    if H:
+        bits = x.table.copy()
+        bits[::3, ::5] = 0x7FC0                            # NaN
+        bits[1::3, ::7] = 0x7F80                           # +inf
+        tab = U.dev(bits.view(np.int16)).view(torch.bfloat16)
+    buf = {n: torch.full((2 * pad + B * budget,), 7, dtype=dt, device="cuda")
+           for n, dt in (("parent", torch.int32), ("token", torch.int32), ("joint", torch.float32))}
+    out = {n: t[pad:-pad].view(B, budget) for n, t in buf.items()}
+    par, tok, jnt, nn = T.tree_build(U.dev(logits), U.dev(x.root), tab, U.dev(x.hot_vocab) if H else None,
+                                     U.dev(x.hot_index) if H else None, k=k, budget=budget, **out)
+    torch.cuda.synchronize()
+    for n, t in buf.items():
+        assert (t[:pad] == 7).all() and (t[-pad:] == 7).all(), f"{n}: written outside"
+    assert (nn == budget).all()
+    par, tok = par.cpu().numpy(), tok.cpu().numpy()
+    assert (par >= -1).all() and (par < np.arange(budget)).all()
+    assert (tok >= -1).all() and (tok < V).all()
+
+
 # ---------------------------------------------------------------- re-sampling (Alg. 2)
 def run_resample(T, x, bonus, alen, r, budget=None, k=None):
     budget = x.budget if budget is None else budget
