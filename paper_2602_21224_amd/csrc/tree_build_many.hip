@@ -12,6 +12,8 @@
 // joint probabilities are equal to within about 1e-13.
 #include "tv_internal.h"
 
+#include <climits>
+
 namespace tv {
 namespace {
 
@@ -618,7 +620,7 @@ __global__ __launch_bounds__(kPruneThreads) void tb_prune_kernel(
     const int32_t *__restrict__ node_par, const double *__restrict__ node_joint,
     int32_t *__restrict__ parent, int32_t *__restrict__ token, float *__restrict__ joint,
     int32_t *__restrict__ num_nodes) {
-    __shared__ double s_j[kPruneSlots];
+    __shared__ long long s_j[kPruneSlots];           // keys of joint probabilities
     __shared__ short s_i[kPruneSlots];
     __shared__ short s_new[kPruneSlots];
     __shared__ int s_warp[kPruneThreads / kWave];
@@ -629,7 +631,7 @@ __global__ __launch_bounds__(kPruneThreads) void tb_prune_kernel(
     int P2 = 1;
     while (P2 < n) P2 <<= 1;
     for (int i = tid; i < P2; i += kPruneThreads) {
-        s_j[i] = i < n ? node_joint[nb + i] : -1.0;
+        s_j[i] = i < n ? joint_key(node_joint[nb + i]) : LLONG_MIN;
         s_i[i] = (short)i;
     }
     __syncthreads();
@@ -640,7 +642,7 @@ __global__ __launch_bounds__(kPruneThreads) void tb_prune_kernel(
                 const int pr = i ^ stride;
                 if (pr > i) {
                     const bool desc = (i & size) == 0;
-                    const double ja = s_j[i], jb = s_j[pr];
+                    const long long ja = s_j[i], jb = s_j[pr];
                     const int ia = s_i[i], ib = s_i[pr];
                     const bool a_first = ja > jb || (ja == jb && ia < ib);
                     if (a_first != desc) {
