@@ -267,7 +267,7 @@ __device__ const double kExp2Table[kExpTab] = {
 // of kExp2Table in LDS). ln2/64 is split into kL1 (its 37 leading significant
 // bits, so N kL1 is exact for |N| < 2^16) and kL2 = ln2/64 - kL1 rounded to
 // double. N is rounded by adding 1.5 2^52, whose low word then holds it.
-// Arguments below -700 (and -inf, NaN) count as -700: 1e-304, below any
+// For sums only: arguments below -700 (and -inf, NaN) count as -700: 1e-304, below any
 // rounding of a sum whose largest term is 1. About 1 ulp.
 __device__ __forceinline__ double exp_nonpos(double x, const double *tab) {
     const double kInvL = 92.33248261689366;          // 64 / ln2
@@ -619,7 +619,9 @@ __device__ __forceinline__ void select_step(SelShared &sh, TbParts rows, int seg
                          sh.wcol[0][wave]);
             if (lane < k) {                              // lane i: child i; a rank without a key has no token
                 const unsigned long long key = sh.win[0][wave][lane];
-                const double joint = key == 0ull ? 0.0 : sl.joint * (exp_nonpos((double)key_value(key) - (double)m, tab) / s);
+                // exp, not exp_nonpos: a masked token's probability is 0 (or a
+                // subnormal), and its rank among its equals is its place
+                const double joint = key == 0ull ? 0.0 : sl.joint * (exp((double)key_value(key) - (double)m) / s);
                 sh.joint[j * k + lane] = joint;
                 sh.col[j * k + lane] = key == 0ull ? -1 : sh.wcol[0][wave][lane];
                 if (writer) {

@@ -132,6 +132,31 @@ def test_tree_build_equal_logits(H, k):
     assert (nn.cpu().numpy() == k + 1).all()
 
 
+@pytest.mark.parametrize("mask", [-600.0, -1e4, -3.4028235e38])
+@pytest.mark.parametrize("H,k", [(0, 8), (900, 8), (0, 12), (900, 3)])
+def test_tree_build_masked_logits(oracle_mod, H, k, mask):
+    """A constrained step: two allowed tokens, the others at one finite low value.
+    Their probabilities underflow (to 0, or in products), so the budget beyond the
+    live nodes goes to the nodes created first, as in the oracle. All its ties are
+    exact on both sides, so no margin applies."""
+    T = U.require_gpu()
+    print(f"case masked H={H} k={k} mask={mask}", flush=True)
+    x = W.make_tree_build_inputs("mask", 160 + k, B=3, S=4, V=2500, H=H, k=k, budget=64)
+    rng = np.random.default_rng(k)
+    logits = np.full_like(x.logits, mask)
+    for b in range(x.B):
+        for i in range(x.S):
+            keep = rng.choice(x.V, 2, replace=False)
+            logits[b, i, keep] = x.logits[b, i, keep]
+    x.logits[:] = logits
+    want = oracle_mod.tree_build(x.logits, x.root, x.table, x.hot_vocab, k, x.budget)
+    got = run_gpu(T, x)
+    np.testing.assert_array_equal(got[3], want[3])
+    np.testing.assert_array_equal(got[1], want[1])
+    np.testing.assert_array_equal(got[0], want[0])
+    np.testing.assert_allclose(got[2], want[2], rtol=1e-6, atol=1e-45)
+
+
 def test_tree_build_narrative(oracle_mod):
     """The worked example of §5.2 (golden fixture) on the GPU."""
     T = U.require_gpu()
