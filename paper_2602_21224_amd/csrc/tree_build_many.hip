@@ -10,7 +10,7 @@
 // Probabilities and joint probabilities are fp64 (exp and sums in double), so
 // frontier and pruning decisions agree with an fp64 evaluation unless two
 // joint probabilities are equal to within about 1e-13.
-#include "tv_internal.h"
+#include "tree_build_common.h"
 
 #include <climits>
 
@@ -46,75 +46,27 @@ struct TbFrontier {
     TbSlot slot[kTbMaxK];
 };
 
-// Hot row of token t (-1 when it has none).
-__device__ __forceinline__ int hot_row(const int32_t *hot_index, int t, int V, int H) {
-    int h = (H > 0 && t >= 0 && t < V) ? hot_index[t] : -1;
-    return h >= H ? -1 : h;
-}
-
-__device__ __forceinline__ unsigned long long umax64(unsigned long long a, unsigned long long b) {
-    return a > b ? a : b;
-}
-
-__device__ __forceinline__ float key_value(unsigned long long key) {
-    const unsigned int k = (unsigned int)(key >> 32);
-    return __uint_as_float((k & 0x80000000u) ? (k & 0x7FFFFFFFu) : ~k);
-}
-
-__device__ __forceinline__ int key_index(unsigned long long key) {
-    return (int)(0xFFFFFFFFu - (unsigned int)key);
-}
-
-__device__ __forceinline__ double exp_nonpos(double x, const double *tab);
-
 // Running (max, sum of exp(x - max)) of one thread, fp64 sums; a batch of
 // values is folded in with one rescale, without per-value branches. tab: the
-// 2^(j/32) table of exp_nonpos.
+// table of exp_nonpos.
 struct OnlineSum {
-    float m = -__builtin_huge_valf();
+    float m = kNegInf;
     double s = 0.0;
     __device__ __forceinline__ void merge(float m2, double s2, const double *tab) {
-        if (m2 == -__builtin_huge_valf()) return;
-        if (m == -__builtin_huge_valf()) { m = m2; s = s2; return; }
+        if (m2 == kNegInf) return;
+        if (m == kNegInf) { m = m2; s = s2; return; }
         const float mn = fmaxf(m, m2);
         s = s * exp_nonpos((double)m - (double)mn, tab) + s2 * exp_nonpos((double)m2 - (double)mn, tab);
         m = mn;
     }
 };
 
-// Cross-lane helpers without LDS: readlane (wave-uniform source lane) and a
-// one-lane shift inside each row of 16 lanes (DPP row_shr:1).
-__device__ __forceinline__ unsigned long long readlane64(unsigned long long v, int src) {
-    const unsigned int lo = __builtin_amdgcn_readlane((int)(unsigned int)v, src);
-    const unsigned int hi = __builtin_amdgcn_readlane((int)(unsigned int)(v >> 32), src);
-    return ((unsigned long long)hi << 32) | lo;
-}
-
+// One-lane shift inside each row of 16 lanes (DPP row_shr:1).
 __device__ __forceinline__ unsigned long long row_shr1_64(unsigned long long v) {
     const int lo = (int)(unsigned int)v, hi = (int)(unsigned int)(v >> 32);
     const unsigned int nlo = __builtin_amdgcn_update_dpp(lo, lo, 0x111, 0xF, 0xF, false);
     const unsigned int nhi = __builtin_amdgcn_update_dpp(hi, hi, 0x111, 0xF, 0xF, false);
     return ((unsigned long long)nhi << 32) | nlo;
-}
-
-// Largest 64-bit key over the wave, by a scan of per-row maxima (no LDS).
-__device__ __forceinline__ unsigned long long wave_max64(unsigned long long v) {
-    #pragma unroll
-    for (int sh = 1; sh < 16; sh <<= 1) {        // row_shr:sh; lanes below sh keep their value
-        const int lo = (int)(unsigned int)v, hi = (int)(unsigned int)(v >> 32);
-        const unsigned int nlo = sh == 1 ? __builtin_amdgcn_update_dpp(lo, lo, 0x111, 0xF, 0xF, false)
-                               : sh == 2 ? __builtin_amdgcn_update_dpp(lo, lo, 0x112, 0xF, 0xF, false)
-                               : sh == 4 ? __builtin_amdgcn_update_dpp(lo, lo, 0x114, 0xF, 0xF, false)
-                                         : __builtin_amdgcn_update_dpp(lo, lo, 0x118, 0xF, 0xF, false);
-        const unsigned int nhi = sh == 1 ? __builtin_amdgcn_update_dpp(hi, hi, 0x111, 0xF, 0xF, false)
-                               : sh == 2 ? __builtin_amdgcn_update_dpp(hi, hi, 0x112, 0xF, 0xF, false)
-                               : sh == 4 ? __builtin_amdgcn_update_dpp(hi, hi, 0x114, 0xF, 0xF, false)
-                                         : __builtin_amdgcn_update_dpp(hi, hi, 0x118, 0xF, 0xF, false);
-        v = umax64(v, ((unsigned long long)nhi << 32) | nlo);
-    }
-    // lane 15 of every row now holds its row's maximum
-    return umax64(umax64(readlane64(v, 15), readlane64(v, 31)),
-                  umax64(readlane64(v, 47), readlane64(v, 63)));
 }
 
 // Largest 32-bit value over the wave: a scan of per-row maxima by DPP row
@@ -127,63 +79,6 @@ __device__ __forceinline__ unsigned int wave_max32(unsigned int v) {
     // lane 15 of every row now holds its row's maximum
     return max(max((unsigned int)__builtin_amdgcn_readlane((int)v, 15), (unsigned int)__builtin_amdgcn_readlane((int)v, 31)),
                max((unsigned int)__builtin_amdgcn_readlane((int)v, 47), (unsigned int)__builtin_amdgcn_readlane((int)v, 63)));
-}
-
-// Whole-wave reductions without LDS: butterflies inside each row of 16 lanes
-// by DPP (swap neighbours, swap pairs, mirror each half row, mirror the row:
-// after each step every lane of the group holds the group's result), then
-// across rows by the row-pair and half-wave swaps. Every lane ends with the
-// result.
-template <int C>
-__device__ __forceinline__ unsigned int dpp32(unsigned int v) {
-    return (unsigned int)__builtin_amdgcn_update_dpp((int)v, (int)v, C, 0xF, 0xF, false);
-}
-template <int C>
-__device__ __forceinline__ double dpp64(double v) {
-    const unsigned long long b = (unsigned long long)__double_as_longlong(v);
-    const unsigned int lo = dpp32<C>((unsigned int)b), hi = dpp32<C>((unsigned int)(b >> 32));
-    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
-}
-constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E, kDppHalfMirror = 0x141, kDppMirror = 0x140;
-
-__device__ __forceinline__ float wave_allmax(float v) {
-    v = fmaxf(v, __uint_as_float(dpp32<kDppXor1>(__float_as_uint(v))));
-    v = fmaxf(v, __uint_as_float(dpp32<kDppXor2>(__float_as_uint(v))));
-    v = fmaxf(v, __uint_as_float(dpp32<kDppHalfMirror>(__float_as_uint(v))));
-    v = fmaxf(v, __uint_as_float(dpp32<kDppMirror>(__float_as_uint(v))));
-    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    v = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
-    const auto h = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    return fmaxf(__uint_as_float(h[0]), __uint_as_float(h[1]));
-}
-
-__device__ __forceinline__ double wave_allsum(double v) {
-    v += dpp64<kDppXor1>(v);
-    v += dpp64<kDppXor2>(v);
-    v += dpp64<kDppHalfMirror>(v);
-    v += dpp64<kDppMirror>(v);
-    #pragma unroll
-    for (int half = 0; half < 2; ++half) {         // row pairs, then the wave's halves
-        const unsigned long long b = (unsigned long long)__double_as_longlong(v);
-        const unsigned int lo = (unsigned int)b, hi = (unsigned int)(b >> 32);
-        const auto l = half == 0 ? __builtin_amdgcn_permlane16_swap(lo, lo, false, false)
-                                 : __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
-        const auto h = half == 0 ? __builtin_amdgcn_permlane16_swap(hi, hi, false, false)
-                                 : __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
-        v = __longlong_as_double((long long)(((unsigned long long)h[0] << 32) | l[0])) +
-            __longlong_as_double((long long)(((unsigned long long)h[1] << 32) | l[1]));
-    }
-    return v;
-}
-
-// Sum over aligned groups of n consecutive lanes (n = 1, 2, 4, 8 or 16,
-// wave-uniform); every lane of a group ends with the group's sum.
-__device__ __forceinline__ int group_sum(int v, int n) {
-    if (n >= 2) v += (int)dpp32<kDppXor1>((unsigned int)v);
-    if (n >= 4) v += (int)dpp32<kDppXor2>((unsigned int)v);
-    if (n >= 8) v += (int)dpp32<kDppHalfMirror>((unsigned int)v);
-    if (n >= 16) v += (int)dpp32<kDppMirror>((unsigned int)v);
-    return v;
 }
 
 // A wave's top-k list, distributed over lanes: lane j < k holds the (j+1)-th
@@ -208,38 +103,6 @@ struct WaveTopK {
     }
 };
 
-// exp(x) for x <= 0 in double precision, by Tang's table-driven method (ACM
-// TOMS 15(2), 1989): x = (32 n + j) ln2/32 + r with |r| <= ln2/64, so
-// e^x = 2^(n >> 5) 2^(j/32) e^r, j = n & 31; e^r - 1 from its degree-6 Taylor
-// polynomial (truncation below 2e-17 on that interval); 2^(j/32) from a
-// 32-entry table (tab, filled by fill_exp2_table). ln2/32 is split into
-// kL1 (its 37 leading significant bits, so N kL1 is exact for |N| < 2^16) and
-// kL2 = ln2/32 - kL1 rounded to double. Arguments below -745 (and -inf) give 0.
-// About 1 ulp, against about 45 instructions for the library's exp.
-__device__ __forceinline__ double exp_nonpos(double x, const double *tab) {
-    const double kInvL = 46.16624130844683;          // 32 / ln2
-    const double kL1 = 0.021660849392446835;
-    const double kL2 = 5.145609244655338e-14;
-    const double N = __builtin_rint(x * kInvL);
-    double r = __builtin_fma(-N, kL1, x);
-    r = __builtin_fma(-N, kL2, r);
-    double q = __builtin_fma(r, 1.0 / 720.0, 1.0 / 120.0);
-    q = __builtin_fma(q, r, 1.0 / 24.0);
-    q = __builtin_fma(q, r, 1.0 / 6.0);
-    q = __builtin_fma(q, r, 0.5);
-    q = __builtin_fma(q, r, 1.0);
-    q *= r;                                          // e^r - 1
-    const int n = x < -745.0 ? 0 : (int)N;
-    const double t = tab[n & 31];
-    const double y = __builtin_ldexp(__builtin_fma(t, q, t), n >> 5);
-    return x < -745.0 ? 0.0 : y;
-}
-
-// 2^(j/32), j = 0..31, into LDS for exp_nonpos; the caller synchronises.
-__device__ __forceinline__ void fill_exp2_table(double *tab) {
-    if (threadIdx.x < 32) tab[threadIdx.x] = exp2((double)threadIdx.x / 32.0);
-}
-
 // One chunk of a thread's candidates, all in registers: x[u] is the value of
 // vocabulary id id(u), -inf when it is not a candidate. Folds their
 // (max, fp64 sum of exp(x - max)) into os and their k largest keys into the
@@ -249,7 +112,6 @@ __device__ __forceinline__ void fill_exp2_table(double *tab) {
 template <int U, typename Id>
 __device__ __forceinline__ void fold_chunk(const float (&x)[U], Id id, int k, int lane,
                                            const double *tab, OnlineSum &os, WaveTopK &tk) {
-    constexpr float kNegInf = -__builtin_huge_valf();
     float m = kNegInf;
     unsigned int kv[U];
     unsigned int kmax = 0u;
@@ -295,7 +157,7 @@ __device__ void block_reduce_part(OnlineSum os, const WaveTopK &tk, int k, TbPar
     // the wave's maximum first, then each lane's sum rescaled to it once and
     // the sums added (one exponential per lane instead of one per merge)
     const float wm = wave_allmax(os.m);
-    const double ws = wave_allsum(os.m == -__builtin_huge_valf() ? 0.0 : os.s * exp_nonpos((double)os.m - (double)wm, tab));
+    const double ws = wave_allsum(os.m == kNegInf ? 0.0 : os.s * exp_nonpos((double)os.m - (double)wm, tab));
     os.m = wm;
     os.s = ws;
     if (lane == 0) { s_m[wave] = os.m; s_s[wave] = os.s; }
@@ -326,27 +188,9 @@ __device__ void block_reduce_part(OnlineSum os, const WaveTopK &tk, int k, TbPar
 __device__ __forceinline__ void wave_reduce_part(const OnlineSum &os, const WaveTopK &tk, int k,
                                                  int lane, TbPart *out, const double *tab) {
     const float wm = wave_allmax(os.m);
-    const double ws = wave_allsum(os.m == -__builtin_huge_valf() ? 0.0 : os.s * exp_nonpos((double)os.m - (double)wm, tab));
+    const double ws = wave_allsum(os.m == kNegInf ? 0.0 : os.s * exp_nonpos((double)os.m - (double)wm, tab));
     if (lane == 0) { out->m = wm; out->pad = 0; out->s = ws; }
     if (lane < kTbMaxK) out->key[lane] = lane < k ? tk.w : 0ull;
-}
-
-// Steps of sequence b: logits rows [first, first + count). A first tree uses all
-// S rows. A re-sampled tree (Alg. 2; accept_len given) starts after the first
-// rejected position -- the accepted path counts the root, so that position is
-// accept_len and the remaining rows are accept_len .. S-1 -- and is the single
-// ground-truth node unless more than r rows remain. A sequence that verified
-// nothing has no tree (count -1).
-struct TbWindow {
-    int first, count;
-};
-
-__device__ __forceinline__ TbWindow tb_window(const int32_t *accept_len, int b, int S, int r) {
-    if (!accept_len) return {0, S};
-    const int a = accept_len[b];
-    if (a <= 0) return {0, -1};
-    const int remain = S - a;
-    return {min(a, S), remain > r ? remain : 0};
 }
 
 // Node-independent part of every (sequence, step): the non-hot tokens of the
@@ -359,7 +203,7 @@ __global__ __launch_bounds__(kTbThreads) void tb_rows_kernel(
     TbPart *__restrict__ rows, float *__restrict__ hot_logits, int max_nodes,
     int32_t *__restrict__ node_tok, int32_t *__restrict__ node_par,
     double *__restrict__ node_joint, TbFrontier *__restrict__ frontier) {
-    __shared__ double s_exp2[32];
+    __shared__ double s_exp2[kExpTab];
     fill_exp2_table(s_exp2);
     __syncthreads();
     const int row = blockIdx.x, seg = blockIdx.y;
@@ -386,7 +230,7 @@ __global__ __launch_bounds__(kTbThreads) void tb_rows_kernel(
         #pragma unroll
         for (int u = 0; u < kTbChunk; ++u) {     // outside, or hot (handled per node): unused
             const bool use = vb + u * kTbThreads < v1 && !(hv[u] >= 0 && hv[u] < H);
-            xv[u] = use ? xv[u] : -__builtin_huge_valf();
+            xv[u] = use ? xv[u] : kNegInf;
         }
         fold_chunk(xv, [&](int u) { return vb + u * kTbThreads; }, k, lane, s_exp2, os, tk);
     }
@@ -406,7 +250,7 @@ __global__ __launch_bounds__(kTbThreads) void tb_rows_kernel(
                 hv[u] = c < c1 ? hot_vocab[c] : -1;
             }
             #pragma unroll
-            for (int u = 0; u < kG; ++u) hx[u] = (hv[u] >= 0 && hv[u] < V) ? l[hv[u]] : -__builtin_huge_valf();
+            for (int u = 0; u < kG; ++u) hx[u] = (hv[u] >= 0 && hv[u] < V) ? l[hv[u]] : kNegInf;
             #pragma unroll
             for (int u = 0; u < kG; ++u)
                 if (cb + u * kTbThreads < c1) lh[cb + u * kTbThreads] = hx[u];
@@ -439,7 +283,7 @@ __global__ __launch_bounds__(kExpThreads) void tb_expand_kernel(
     const TbWindow win = tb_window(accept_len, b, S, r);
     if (step >= win.count) return;                 // this sequence's tree is complete
     if (j >= count) return;                        // no such frontier node at this step
-    __shared__ double s_exp2[32];
+    __shared__ double s_exp2[kExpTab];
     fill_exp2_table(s_exp2);
     __syncthreads();
     const float *lh = hot_logits + ((size_t)b * S + win.first + step) * H;
@@ -487,7 +331,7 @@ __global__ __launch_bounds__(kExpThreads) void tb_expand_kernel(
             for (int u = 0; u < kTbChunk; ++u) {
                 if (h >= 0) xv[u] += __uint_as_float(rv[u] << 16);
                 const bool use = (full || cb + u * kExpThreads < c1) && (unsigned int)vv[u] < (unsigned int)V;
-                xv[u] = use ? xv[u] : -__builtin_huge_valf();
+                xv[u] = use ? xv[u] : kNegInf;
             }
             fold_chunk(xv, [&](int u) { return vv[u]; }, k, lane, s_exp2, os, tk);
         };
@@ -535,7 +379,7 @@ __global__ __launch_bounds__(kTbMaxK * kWave) void tb_select_kernel(
         const TbSlot sl = fr->slot[j];
         const int f = sl.node;
         // every load of this node is issued before any is used
-        float pm = -__builtin_huge_valf();
+        float pm = kNegInf;
         double ps = 0.0;
         if (lane < nparts) {
             const TbPart *pp = lane < segs ? rp + lane : cp + (lane - segs);
@@ -555,7 +399,7 @@ __global__ __launch_bounds__(kTbMaxK * kWave) void tb_select_kernel(
         }
         const double pj = sl.joint;
         const float m = wave_allmax(pm);
-        const double s = wave_allsum(pm == -__builtin_huge_valf() ? 0.0 : ps * exp((double)pm - (double)m));
+        const double s = wave_allsum(pm == kNegInf ? 0.0 : ps * exp((double)pm - (double)m));
         // rank r's key goes to lane r; the children's probabilities are then
         // computed by lanes 0..k-1 at once
         unsigned long long mine = 0ull;

@@ -44,12 +44,6 @@ __device__ __forceinline__ unsigned long long pack_key(unsigned int key, unsigne
     return ((unsigned long long)key << 32) | (unsigned long long)(0xFFFFFFFFu - idx);
 }
 
-// Joint probabilities in the order the builder ranks them by. They are not
-// negative, so their bits order as they do, and a NaN (only logits that are not
-// finite give one) has a place in the order too: ranks by counting are always a
-// permutation, so no slot or node that a later step indexes by stays unwritten.
-__device__ __forceinline__ long long joint_key(double j) { return __double_as_longlong(j); }
-
 // Launch geometry and workspace layout of the tree builder. parts and frontier
 // are carved twice (double buffered over the steps).
 struct TreeBuildPlan {
