@@ -20,7 +20,9 @@
 // only the rows (tb_rows_kernel) and tb_finish_kernel run.
 //
 // Decisions: candidates are ranked by the fp32 sum l + r (the precision of the
-// logits; ties to the lower vocabulary id) through a packed 64-bit key.
+// logits; ties to the lower vocabulary id) through a packed 64-bit key; -inf and
+// NaN are no candidates, so a node with fewer than k others has children without
+// a token (-1, probability 0).
 // Probabilities and joint probabilities are fp64 (exp and sums in double), so
 // frontier and pruning decisions agree with an fp64 evaluation unless two
 // joint probabilities are equal to within about 1e-13.
@@ -281,7 +283,7 @@ __device__ __forceinline__ void reduce_row(RowsShared &sh, const float *__restri
                 #pragma unroll 1
                 for (int v = vb + tid; v < min(v1, vb + U * kTbThreads); v += kTbThreads) {
                     if (H > 0 && (unsigned)hot_index[v] < (unsigned)H) continue;
-                    const unsigned long long key = pack_key(order_key(l[v]), (unsigned)v);
+                    const unsigned long long key = l[v] >= fl ? pack_key(order_key(l[v]), (unsigned)v) : 0ull;
                     best = key < prev ? umax64(best, key) : best;
                 }
                 best = wave_max64(best);
@@ -680,7 +682,7 @@ __global__ __launch_bounds__(kTbThreads, CPL > 4 ? 2 : 4) void tb_step_kernel(St
                     for (int cl = lane; cl < kCols; cl += kWave) {
                         const float x = value_at(cl);
                         const unsigned long long key = pack_key(order_key(x), (unsigned)s_id[cl]);
-                        if (x != kNegInf && key < prev && key > best) {
+                        if (x >= fl && key < prev && key > best) {
                             best = key;
                             bc = cl;
                         }

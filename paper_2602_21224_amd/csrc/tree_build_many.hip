@@ -118,7 +118,7 @@ __device__ __forceinline__ void fold_chunk(const float (&x)[U], Id id, int k, in
     #pragma unroll
     for (int u = 0; u < U; ++u) {
         m = fmaxf(m, x[u]);
-        kv[u] = x[u] != kNegInf ? order_key(x[u]) : 0u;
+        kv[u] = x[u] > kNegInf ? order_key(x[u]) : 0u;     // no key for NaN either
         kmax = max(kmax, kv[u]);
     }
     if (m != kNegInf) {

@@ -312,6 +312,36 @@ def test_tree_build_not_finite_stays_in_bounds(H, k):
     assert (tok >= -1).all() and (tok < V).all()
 
 
+@pytest.mark.parametrize("ties", [False, True])
+@pytest.mark.parametrize("H,k", [(0, 3), (3000, 8), (3000, 12)])
+def test_tree_build_nan_is_no_candidate(H, k, ties):
+    """Beside finite candidates NaN logits are left out of the tree and of the
+    sums, whichever way the candidates are ranked: a few lie above the others, or
+    (ties) more are equal than any candidate list holds."""
+    T = U.require_gpu()
+    print(f"case nan H={H} k={k} ties={ties}", flush=True)
+    V, B = 5000, 2
+    rng = np.random.default_rng(H + k)
+    hot = rng.permutation(V)[:H].astype(np.int32)
+    index = np.full(V, -1, np.int32)
+    index[hot] = np.arange(H, dtype=np.int32)
+    logits = np.full((B, 1, V), 0.5, np.float32)
+    if not ties:
+        logits += rng.random((B, 1, V), dtype=np.float32)
+    nan = rng.random((B, 1, V)) < 0.2
+    logits[nan] = np.nan
+    tab = torch.zeros((H, H), dtype=torch.bfloat16, device="cuda") if H else None
+    par, tok, jnt, nn = T.tree_build(U.dev(logits), U.dev(np.array([7, 4999], np.int32)), tab,
+                                     U.dev(hot) if H else None, U.dev(index) if H else None, k=k, budget=k + 1)
+    torch.cuda.synchronize()
+    for b in range(B):
+        x = np.where(nan[b, 0], -np.inf, logits[b, 0].astype(np.float64))
+        order = np.lexsort((np.arange(V), -x))[:k]
+        assert tok[b, 1:].tolist() == order.tolist()
+        p = np.exp(x[order] - x.max()) / np.exp(x - x.max()).sum()
+        np.testing.assert_allclose(jnt[b, 1:].cpu().numpy(), p, rtol=1e-6)
+
+
 # ---------------------------------------------------------------- re-sampling (Alg. 2)
 def run_resample(T, x, bonus, alen, r, budget=None, k=None):
     budget = x.budget if budget is None else budget
