@@ -520,7 +520,7 @@ struct StepArgs {
 // Bound by the chain partials -> children -> table row -> columns; two workgroups
 // share a CU, so the second kind costs little beside the first.
 template <int CPL, int U, int RU>
-__global__ __launch_bounds__(kTbThreads, CPL > 4 ? 2 : 4) void tb_step_kernel(StepArgs p) {
+__global__ __launch_bounds__(kTbThreads, 4) void tb_step_kernel(StepArgs p) {
     constexpr int kCols = StepShared<U>::kCols;
     constexpr int kG = kCols / kTbThreads;           // columns gathered per thread
     __shared__ union Sh {
@@ -990,12 +990,9 @@ hipError_t launch_tree_build(const float *logits, const int32_t *root_token,
                           dim3(kTbThreads), s, a);
     }
     if (pl.chunks > 0) {
-        auto pick = [&](auto cpl) {
-            constexpr int C = decltype(cpl)::value;
-            return pl.col_u == 32 ? (pl.row_u == 16 ? tb_step_kernel<C, 32, 16> : tb_step_kernel<C, 32, 4>)
-                                  : (pl.row_u == 16 ? tb_step_kernel<C, 16, 16> : tb_step_kernel<C, 16, 4>);
-        };
-        auto sk = per_lane <= 4 ? pick(std::integral_constant<int, 4>()) : pick(std::integral_constant<int, 8>());
+        auto sk = per_lane > 4     ? tb_step_kernel<8, 32, 16>       // the plan has no small parts then
+                  : pl.col_u == 32 ? (pl.row_u == 16 ? tb_step_kernel<4, 32, 16> : tb_step_kernel<4, 32, 4>)
+                                   : (pl.row_u == 16 ? tb_step_kernel<4, 16, 16> : tb_step_kernel<4, 16, 4>);
         for (int i = 0; i < S && e == hipSuccess; ++i) {
             a.step = i;
             a.parts_in = parts[(i + 1) & 1];

@@ -157,6 +157,53 @@ def test_tree_build_masked_logits(oracle_mod, H, k, mask):
     np.testing.assert_allclose(got[2], want[2], rtol=1e-6, atol=1e-45)
 
 
+def shared_row_inputs(seed, B, S, V, H, k, budget):
+    """Inputs whose table rows are all the same row (so that a large table costs
+    the oracle one row): the inputs and the bf16 table on the GPU."""
+    x = W.make_tree_build_inputs("shared", seed, B=B, S=S, V=V, H=64, k=k, budget=budget)
+    rng = np.random.default_rng(seed)
+    x.hot_vocab = rng.permutation(V)[:H].astype(np.int32)
+    x.hot_index = np.full(V, -1, np.int32)
+    x.hot_index[x.hot_vocab] = np.arange(H, dtype=np.int32)
+    row = W.f32_to_bf16_bits(rng.standard_normal(H, dtype=np.float32))
+    x.table = np.broadcast_to(row, (H, H))
+    x.root[0] = x.hot_vocab[5]
+    return x, U.dev(row.view(np.int16)).view(torch.bfloat16).expand(H, H).contiguous()
+
+
+def check_shared_row(oracle_mod, T, x, tab, alen=None):
+    a = (U.dev(x.hot_vocab), U.dev(x.hot_index))
+    margins = []
+    if alen is None:
+        want = oracle_mod.tree_build(x.logits, x.root, x.table, x.hot_vocab, x.k, x.budget, margins)
+        got = T.tree_build(U.dev(x.logits), U.dev(x.root), tab, *a, k=x.k, budget=x.budget)
+    else:
+        want = oracle_mod.resample(x.logits, x.root, alen, x.table, x.hot_vocab, x.k, 1, x.budget, margins)
+        got = T.tree_resample(U.dev(x.logits), U.dev(x.root), U.dev(alen), tab, *a, k=x.k, r=1,
+                              budget=x.budget)
+    torch.cuda.synchronize()
+    assert min(margins) > 1e-9
+    par, tok, jnt, nn = [t.cpu().numpy() for t in got]
+    np.testing.assert_array_equal(nn, want[3])
+    np.testing.assert_array_equal(tok, want[1])
+    np.testing.assert_array_equal(par, want[0])
+    np.testing.assert_allclose(jnt, want[2], rtol=1e-6)
+
+
+@pytest.mark.parametrize("H,k,alen", [
+    (28673, 8, None),          # 19 segments and 15 chunks of 8 keys: more than 4 keys per lane
+    (28680, 5, [1, 2]),        # re-sampling, wide table loads
+])
+def test_tree_build_many_parts(oracle_mod, H, k, alen):
+    """A vocabulary and hot set whose parts hold more than 256 candidate keys per
+    node: the selection holds eight per lane."""
+    T = U.require_gpu()
+    print(f"case many parts H={H} k={k} accept_len={alen}", flush=True)
+    B = len(alen) if alen else 1
+    x, tab = shared_row_inputs(170 + k, B, 4 if alen else 3, 151936, H, k, 40)
+    check_shared_row(oracle_mod, T, x, tab, None if alen is None else np.array(alen, np.int32))
+
+
 def test_tree_build_narrative(oracle_mod):
     """The worked example of §5.2 (golden fixture) on the GPU."""
     T = U.require_gpu()
