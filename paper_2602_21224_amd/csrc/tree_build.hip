@@ -29,8 +29,10 @@
 //
 // Top-k of a set held in registers: the maxima of k or more disjoint groups of
 // it are k candidates, so none of the k largest lies below the smallest of
-// those maxima. The entries at or above that floor (about 22) are listed in LDS and ranked by counting; a list that would overflow
-// (many equal entries) is replaced by k rounds of a plain maximum. The list holds
+// those maxima. The entries at or above that floor (about 22) are listed in LDS
+// and ranked by counting; a list that would overflow (many equal entries) is made
+// again from whole keys, value and vocabulary id, above the k-th largest of all
+// lanes' maxima, which no more than k lanes reach. The list holds
 // 256 entries: of 2048 random ones, fewer than one set in a million has more at
 // or above its floor. (With 64, one wave in 700 did, and its rounds set the time
 // of nearly every step: 38 us against 22.)
@@ -49,7 +51,7 @@ namespace {
 constexpr int kTbThreads = 512;            // 8 waves: one per frontier node (k <= 8)
 constexpr int kTbWaves = kTbThreads / kWave;
 constexpr int kTbList = 4 * kWave;         // listed candidates of one wave
-constexpr int kRowsList = 512;      // listed candidates of a rows workgroup
+constexpr int kRowsList = 512;             // listed candidates of a rows workgroup
 constexpr int kMaxParts = 32;              // most segments of a row, most chunks of the hot columns
 constexpr int kPruneSlots = 4096;          // >= 1 + k + (S - 1) k^2 for k, S <= 16
 constexpr int kBuckets = 1024;             // of joint probabilities, for the pruning
@@ -124,6 +126,18 @@ __device__ __forceinline__ unsigned long long wave_floor64(unsigned long long v)
         v = umin64(((unsigned long long)h[0] << 32) | l[0], ((unsigned long long)h[1] << 32) | l[1]);
     }
     return v;
+}
+
+// A floor for lists of whole keys: the k-th largest of the lanes' largest keys (1
+// when fewer lanes have any). Keys have no equals, so only k lanes hold keys at
+// or above it.
+__device__ __forceinline__ unsigned long long wave_kth64(unsigned long long v, int k) {
+    unsigned long long f = 0ull;
+    for (int q = 0; q < k; ++q) {
+        f = wave_max64(v);
+        if (v == f) v = 0ull;
+    }
+    return umax64(f, 1ull);
 }
 
 // Lanes of `mask` below this one.
@@ -201,7 +215,7 @@ struct RowsShared {
     double exp2[kExpTab];
     float gm[kTbWaves];                              // the waves' maxima: 8 groups
     double sum[kTbWaves];
-    unsigned long long list[kRowsList], best[kTbWaves], win[kTbMaxK];
+    unsigned long long list[kRowsList], win[kTbMaxK];
     int n;
 };
 
@@ -217,7 +231,7 @@ __device__ __forceinline__ void reduce_row(RowsShared &sh, const float *__restri
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
     double *const s_exp2 = sh.exp2, *const s_sum = sh.sum;
     float *const s_gm = sh.gm;
-    unsigned long long *const s_list = sh.list, *const s_best = sh.best, *const s_win = sh.win;
+    unsigned long long *const s_list = sh.list, *const s_win = sh.win;
     int &s_n = sh.n;
     fill_exp2_table(s_exp2);
     if (tid < kTbMaxK) s_win[tid] = 0ull;
@@ -272,33 +286,40 @@ __device__ __forceinline__ void reduce_row(RowsShared &sh, const float *__restri
                 s_list[at] = pack_key(order_key(xv[u]), (unsigned)(vb + u * kTbThreads + tid));
         }
         __syncthreads();
-        const int n = s_n;
-        if (n > kRowsList) {
-            // too many at the floor: k rounds of the workgroup's largest key
-            // below the previous one (read again: keys in registers would cost the
-            // common path its registers)
-            unsigned long long prev = ~0ull;
-            for (int q = 0; q < k; ++q) {
-                unsigned long long best = 0ull;
-                #pragma unroll 1
-                for (int v = vb + tid; v < min(v1, vb + U * kTbThreads); v += kTbThreads) {
-                    if (H > 0 && (unsigned)hot_index[v] < (unsigned)H) continue;
-                    const unsigned long long key = l[v] >= fl ? pack_key(order_key(l[v]), (unsigned)v) : 0ull;
-                    best = key < prev ? umax64(best, key) : best;
-                }
-                best = wave_max64(best);
-                if (lane == 0) s_best[wave] = best;
-                __syncthreads();
-                prev = 0ull;
-                #pragma unroll
-                for (int w = 0; w < kTbWaves; ++w) prev = umax64(prev, s_best[w]);
-                __syncthreads();
-                if (tid == 0) s_list[q] = prev;
+        int nl = s_n;
+        if (nl > kRowsList) {
+            // Many equal values at the floor (a masked vocabulary): again by whole
+            // keys, above the k-th largest of the threads' largest keys, which the
+            // waves' k largest of them give (k U keys at most).
+            auto key = [&](int u) {
+                return xv[u] > kNegInf ? pack_key(order_key(xv[u]), (unsigned)(vb + u * kTbThreads + tid)) : 0ull;
+            };
+            unsigned long long c = 0ull;
+            #pragma unroll
+            for (int u = 0; u < U; ++u) c = umax64(c, key(u));
+            for (int q = 0; q < 8; ++q) {
+                const unsigned long long best = q < k ? wave_max64(c) : 0ull;
+                if (c == best) c = 0ull;
+                if (lane == 0) s_list[wave * 8 + q] = best;
             }
             __syncthreads();
+            if (tid == 0) s_n = 0;
+            const unsigned long long kfl = wave_kth64(s_list[lane], k);
+            __syncthreads();
+            #pragma unroll
+            for (int u = 0; u < U; ++u) {
+                tie(xv[u]);                          // the first pass's tests are not kept
+                const unsigned long long mask = __ballot(key(u) >= kfl);
+                if (mask == 0ull) continue;          // wave-uniform
+                int at = 0;
+                if (lane == 0) at = atomicAdd(&s_n, __popcll(mask));
+                at = __builtin_amdgcn_readfirstlane(at) + below(mask);
+                if ((mask >> lane) & 1ull) s_list[at] = key(u);
+            }
+            __syncthreads();
+            nl = s_n;
         }
         // rank the listed keys and the earlier passes' winners by counting
-        const int nl = n > kRowsList ? k : n;
         if (tid < 8 && nl + tid < kRowsList) s_list[nl + tid] = 0ull;
         __syncthreads();
         const bool more = vb > v0;                   // earlier passes exist
@@ -412,24 +433,21 @@ __device__ __forceinline__ void select_step(SelShared &sh, TbParts rows, int seg
                 }
                 n += __popcll(mask);
             }
-            if (n > kTbList) {
-                // k rounds of the largest remaining key
-                wave_lds_sync();
-                for (int q = 0; q < k; ++q) {
-                    unsigned long long best = 0ull;
+            if constexpr (CPL * kWave > kTbList) {
+                if (n > kTbList) {                       // by the narrower floor (k CPL keys at most)
+                    const unsigned long long kfl = wave_kth64(lm, k);
+                    n = 0;
                     #pragma unroll
-                    for (int u = 0; u < CPL; ++u) best = umax64(best, cand[u]);
-                    best = wave_max64(best);
-                    #pragma unroll
-                    for (int u = 0; u < CPL; ++u)
-                        if (best != 0ull && cand[u] == best) {
-                            sh.list[wave][q] = best;
-                            sh.lcol[wave][q] = col[u];
-                            cand[u] = 0ull;
+                    for (int u = 0; u < CPL; ++u) {
+                        const unsigned long long mask = __ballot(cand[u] >= kfl);
+                        const int at = n + below(mask);
+                        if (cand[u] >= kfl && at < kTbList) {
+                            sh.list[wave][at] = cand[u];
+                            sh.lcol[wave][at] = col[u];
                         }
-                    if (best == 0ull && lane == 0) sh.list[wave][q] = 0ull;
+                        n = min(n + __popcll(mask), kTbList);
+                    }
                 }
-                n = k;
             }
             wave_lds_sync();
             list_winners(sh.list[wave], sh.lcol[wave], n, k, lane, false, nullptr, nullptr, sh.win[0][wave],
@@ -672,32 +690,28 @@ __global__ __launch_bounds__(kTbThreads, 4) void tb_step_kernel(StepArgs p) {
                 n += __popcll(mask);
             }
             if (n > kTbList) {
-                // k rounds of the largest key below the previous one
-                unsigned long long prev = ~0ull;
-                wave_lds_sync();
-                for (int i = 0; i < k; ++i) {
-                    unsigned long long best = 0ull;
-                    int bc = 0;
-                    #pragma unroll 1
-                    for (int cl = lane; cl < kCols; cl += kWave) {
-                        const float x = value_at(cl);
-                        const unsigned long long key = pack_key(order_key(x), (unsigned)s_id[cl]);
-                        if (x >= fl && key < prev && key > best) {
-                            best = key;
-                            bc = cl;
-                        }
+                // Many equal values at the floor (a node without a table row in a
+                // masked vocabulary): by whole keys (k U at most).
+                auto at_col = [&](int u) { return (u >> 3) * 512 + lane * 8 + (u & 7); };
+                auto key = [&](int u) {
+                    return xv[u] > kNegInf ? pack_key(order_key(xv[u]), (unsigned)s_id[at_col(u)]) : 0ull;
+                };
+                unsigned long long c = 0ull;
+                #pragma unroll
+                for (int u = 0; u < U; ++u) c = umax64(c, key(u));
+                const unsigned long long kfl = wave_kth64(c, k);
+                n = 0;
+                #pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    tie(xv[u]);                      // the first pass's tests are not kept
+                    const unsigned long long x = key(u), mask = __ballot(x >= kfl);
+                    const int at = n + below(mask);
+                    if (x >= kfl && at < kTbList) {
+                        sh.list[wave][at] = x;
+                        sh.lcol[wave][at] = p0 + at_col(u);
                     }
-                    prev = wave_max64(best);
-                    if (best == prev && best != 0ull) {
-                        sh.list[wave][i] = best;
-                        sh.lcol[wave][i] = p0 + bc;
-                    }
-                    if (prev == 0ull && lane == 0) {
-                        sh.list[wave][i] = 0ull;
-                        sh.lcol[wave][i] = 0;
-                    }
+                    n = min(n + __popcll(mask), kTbList);
                 }
-                n = k;
                 wave_lds_sync();
             } else {
                 wave_lds_sync();                     // the listed entries become keys

@@ -142,6 +142,9 @@ def test_tree_build_masked_logits(oracle_mod, H, k, mask):
     T = U.require_gpu()
     print(f"case masked H={H} k={k} mask={mask}", flush=True)
     x = W.make_tree_build_inputs("mask", 160 + k, B=3, S=4, V=2500, H=H, k=k, budget=64)
+    if k == 3:                                             # hot ids in ascending order
+        x.hot_vocab.sort()
+        x.hot_index[x.hot_vocab] = np.arange(H, dtype=np.int32)
     rng = np.random.default_rng(k)
     logits = np.full_like(x.logits, mask)
     for b in range(x.B):
@@ -155,6 +158,18 @@ def test_tree_build_masked_logits(oracle_mod, H, k, mask):
     np.testing.assert_array_equal(got[1], want[1])
     np.testing.assert_array_equal(got[0], want[0])
     np.testing.assert_allclose(got[2], want[2], rtol=1e-6, atol=1e-45)
+
+
+@pytest.mark.parametrize("V", [70000, 300000])
+def test_tree_build_equal_logits_large(V):
+    """The same ties with 16 tokens per thread, in one pass and in two."""
+    T = U.require_gpu()
+    k = 8
+    logits = torch.full((1, 1, V), 2.0, device="cuda")
+    par, tok, jnt, nn = T.tree_build(logits, U.dev(np.array([9], np.int32)), None, None, None, k=k, budget=k + 1)
+    torch.cuda.synchronize()
+    assert tok[0].tolist() == [9] + list(range(k))
+    np.testing.assert_allclose(jnt[0, 1:].cpu().numpy(), 1.0 / V, rtol=1e-6)
 
 
 def shared_row_inputs(seed, B, S, V, H, k, budget):
@@ -202,6 +217,21 @@ def test_tree_build_many_parts(oracle_mod, H, k, alen):
     B = len(alen) if alen else 1
     x, tab = shared_row_inputs(170 + k, B, 4 if alen else 3, 151936, H, k, 40)
     check_shared_row(oracle_mod, T, x, tab, None if alen is None else np.array(alen, np.int32))
+
+
+def test_tree_build_many_parts_list_overflow(oracle_mod):
+    """Every eighth part holds low values only: more keys reach the selection's
+    first floor (the smallest of eight groups' maxima) than its list holds."""
+    T = U.require_gpu()
+    V, H, k = 151936, 43000, 8                 # 19 segments of 7997, 21 chunks of 2048
+    print(f"case many parts overflow V={V} H={H} k={k}", flush=True)
+    x, tab = shared_row_inputs(180, 1, 3, V, H, k, 40)
+    seg = np.arange(V) // 7997
+    low = (x.hot_index < 0) & (seg % 8 == 0)
+    chunk = np.arange(H) // 2048
+    low[x.hot_vocab[(19 + chunk) % 8 == 0]] = True
+    x.logits[:, :, low] -= 60.0
+    check_shared_row(oracle_mod, T, x, tab)
 
 
 def test_tree_build_narrative(oracle_mod):
