@@ -53,7 +53,10 @@ constexpr int kTbWaves = kTbThreads / kWave;
 constexpr int kTbList = 4 * kWave;         // listed candidates of one wave
 constexpr int kRowsList = 512;             // listed candidates of a rows workgroup
 constexpr int kMaxParts = 32;              // most segments of a row, most chunks of the hot columns
-constexpr int kPruneSlots = 4096;          // >= 1 + k + (S - 1) k^2 for k, S <= 16
+constexpr int kMaxBranches = 8;            // most branches of these kernels
+constexpr int kPruneSlots = 1024;          // nodes of an unpruned tree
+static_assert(1 + kMaxBranches + (kTbMaxSteps - 1) * kMaxBranches * kMaxBranches <= kPruneSlots, "pruning slots");
+static_assert(kMaxBranches <= kTbWaves, "one wave per frontier node");
 constexpr int kBuckets = 1024;             // of joint probabilities, for the pruning
 
 // Partial reductions over sets of candidates, contiguous per reader: of each
@@ -351,8 +354,8 @@ __device__ __forceinline__ void reduce_row(RowsShared &sh, const float *__restri
 
 // LDS of a selection.
 struct SelShared {
-    double joint[kTbMaxK * kTbMaxK];                 // the step's children
-    int col[kTbMaxK * kTbMaxK];
+    double joint[kMaxBranches * kMaxBranches];       // the step's children
+    int col[kMaxBranches * kMaxBranches];
     unsigned long long list[kTbWaves][kTbList + 8];  // candidates of a wave; also the expansion's
     int lcol[kTbWaves][kTbList];
     unsigned long long win[2][kTbWaves][kTbMaxK];    // its k largest
