@@ -44,6 +44,7 @@
 #include "tree_build_common.h"
 
 #include <algorithm>
+#include <climits>
 
 namespace tv {
 namespace {
@@ -859,13 +860,22 @@ __global__ __launch_bounds__(kTbThreads) void tb_finish_kernel(
     }
     __syncthreads();
     const int nm = s_nmem;
+    if (tid < 8 && nm + tid < kPruneSlots) s_mj[nm + tid] = LLONG_MIN;   // below every node's
+    __syncthreads();
     for (int x = tid; x < nm; x += kTbThreads) {
         const int i = s_mem[x];
         const long long ki = s_mj[x];
         int rank = 0;
-        for (int q = 0; q < nm && rank < left; ++q) {
-            const long long kq = s_mj[q];
-            rank += (kq > ki || (kq == ki && s_mem[q] < i)) ? 1 : 0;
+        for (int q = 0; q < nm && rank < left; q += 8) {     // eight reads in flight together
+            long long kq[8];
+            int iq[8];
+            #pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                kq[u] = s_mj[q + u];
+                iq[u] = s_mem[q + u];
+            }
+            #pragma unroll
+            for (int u = 0; u < 8; ++u) rank += (kq[u] > ki) | ((kq[u] == ki) & (iq[u] < i));
         }
         if (rank < left) s_new[i] = 1;
     }
