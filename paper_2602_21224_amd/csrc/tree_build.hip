@@ -30,12 +30,14 @@
 // Top-k of a set held in registers: the maxima of k or more disjoint groups of
 // it are k candidates, so none of the k largest lies below the smallest of
 // those maxima. The entries at or above that floor (about 22) are listed in LDS
-// and ranked by counting; a list that would overflow (many equal entries) is made
-// again from whole keys, value and vocabulary id, above the k-th largest of all
-// lanes' maxima, which no more than k lanes reach. The list holds
-// 256 entries: of 2048 random ones, fewer than one set in a million has more at
-// or above its floor. (With 64, one wave in 700 did, and its rounds set the time
-// of nearly every step: 38 us against 22.)
+// and ranked by counting; a long list (many equal entries, or groups without any) is
+// made again from whole keys, value and vocabulary id, above the k-th largest of all
+// lanes' maxima, which no more than k lanes reach. Long is more than 128: of random
+// entries fewer than one set in a million is (more than 64, one in 650). Measured
+// (us per call): 16 sequences, 7 steps, 128256 tokens of which 32768 hot, k 8, all but
+// 64 logits masked to -1e4: 485 with k rounds of a plain maximum in place of the
+// second list, 213 with it; 4 sequences, 7 steps, 2343 tokens of which 201 hot, k 4:
+// 124 with lists of 201 ranked as they are, 71 so.
 //
 // Measured (16 sequences, 7 steps, vocabulary 128256, 32768 hot tokens, k 8):
 // 199 us per call with a launch for all rows and two launches per step, 157 us
@@ -51,8 +53,9 @@ namespace {
 
 constexpr int kTbThreads = 512;            // 8 waves: one per frontier node (k <= 8)
 constexpr int kTbWaves = kTbThreads / kWave;
-constexpr int kTbList = 4 * kWave;         // listed candidates of one wave
-constexpr int kRowsList = 512;             // listed candidates of a rows workgroup
+constexpr int kTbList = 4 * kWave;         // listed candidates of one wave: room,
+constexpr int kTbLong = 2 * kWave;         // and from where on a narrower floor pays
+constexpr int kRowsList = 2 * kWave;       // listed candidates of a rows workgroup
 constexpr int kMaxParts = 32;              // most segments of a row, most chunks of the hot columns
 constexpr int kMaxBranches = 8;            // most branches of these kernels
 constexpr int kPruneSlots = 1024;          // nodes of an unpruned tree
@@ -279,13 +282,16 @@ __device__ __forceinline__ void reduce_row(RowsShared &sh, const float *__restri
         for (int u = 0; u < U; ++u) ps += exp_nonpos((double)xv[u] - (double)pm, s_exp2);
         ps = wave_allsum(ps);
         if (lane == 0) s_sum[wave] = ps;
+        bool full = false;                           // too long already
         #pragma unroll
         for (int u = 0; u < U; ++u) {
             const unsigned long long mask = __ballot(xv[u] >= fl);
-            if (mask == 0ull) continue;              // wave-uniform
+            if (mask == 0ull || full) continue;      // wave-uniform
             int at = 0;
             if (lane == 0) at = atomicAdd(&s_n, __popcll(mask));
-            at = __builtin_amdgcn_readfirstlane(at) + below(mask);
+            at = __builtin_amdgcn_readfirstlane(at);
+            full = at >= kRowsList;
+            at += below(mask);
             if (((mask >> lane) & 1ull) && at < kRowsList)
                 s_list[at] = pack_key(order_key(xv[u]), (unsigned)(vb + u * kTbThreads + tid));
         }
@@ -687,15 +693,16 @@ __global__ __launch_bounds__(kTbThreads, 4) void tb_step_kernel(StepArgs p) {
                 return h >= 0 ? s_x[cl] + __uint_as_float(t << 16) : s_x[cl];
             };
             int n = 0;
-            for (unsigned long long mask; (mask = __ballot(bits != 0u)) != 0ull && n <= kTbList;) {
+            for (unsigned long long mask; (mask = __ballot(bits != 0u)) != 0ull && n <= kTbLong;) {
                 const int at = n + below(mask);
                 if (bits != 0u && at < kTbList) sh.lcol[wave][at] = (__builtin_ctz(bits) << 6) | lane;
                 bits &= bits - 1u;
                 n += __popcll(mask);
             }
-            if (n > kTbList) {
+            if (n > kTbLong) {
                 // Many equal values at the floor (a node without a table row in a
-                // masked vocabulary): by whole keys (k U at most).
+                // masked vocabulary), or lanes without a column (fewer than 512): by
+                // whole keys (k U at most).
                 auto at_col = [&](int u) { return (u >> 3) * 512 + lane * 8 + (u & 7); };
                 auto key = [&](int u) {
                     return xv[u] > kNegInf ? pack_key(order_key(xv[u]), (unsigned)s_id[at_col(u)]) : 0ull;
