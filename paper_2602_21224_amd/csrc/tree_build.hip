@@ -919,6 +919,41 @@ __global__ __launch_bounds__(kTbThreads) void tb_finish_kernel(
 // Workgroups that fill the chip.
 constexpr int kFill = 256;
 
+// Parts of n entries, `per` in each.
+long parts_of(long n, long per) {
+    const long x = (n + per - 1) / per;
+    return n <= 0 ? 0l : x > kMaxParts ? (long)kMaxParts : x;
+}
+
+// Whether a step is one launch, or its launches are separate (tree_build_many.hip).
+// Without hot tokens there are no steps to launch, and these kernels win up to 8
+// branches (256 sequences of 32000 tokens, 5 steps, k 4: 70 against 95 us). With
+// more branches, nodes and selection would take two rounds per wave (k 10, 16
+// sequences 297 against 231 us). Otherwise one launch saves about 10 us per step
+// while its workgroups run at once, two per CU; past that every further round
+// repeats the selection in each of its workgroups and fills few of its waves, as
+// many as there are branches, and the segments' reductions, which weigh more than
+// the chunks, no longer run beside something that waits. Measured (us, one launch
+// per step / separate launches; 7 steps; segments + chunks per sequence):
+//   16 + 16 (128256 tokens, 32768 hot), k 8: 16 sequences 154 / 186, 32 275 / 295;
+//     k 4: 32 sequences 237 / 229; k 2: 8 sequences 97 / 106, 16 136 / 129, 32 234 / 203;
+//   19 + 16 (151936, 32768), k 4: 8 sequences 120 / 123, 16 181 / 153;
+//   16 + 4 (128256, 8192), k 4: 16 sequences 108 / 119, 24 156 / 131; k 8: 16 117 / 146,
+//     64 286 / 236.
+// Where the chunks are most of it (all of 32000 tokens hot: 4 + 16), or with 7 and 8
+// branches as many, separate launches pass over them too often: k 4, 32 sequences
+// 147 / 158, 64 232 / 272; 16 + 16, k 8, 64 sequences 475 / 503. And
+// re-sampled trees use one launch per step: separate launches reduce the rows of
+// the accepted positions too and cannot tell how many steps remain (32 sequences of
+// 128256 tokens, 32768 hot, k 4, 1 to 4 positions accepted: 187 / 226).
+bool one_launch_per_step(bool resample, int B, int V, int H, int k) {
+    if (k > kMaxBranches) return false;
+    const long segs = parts_of(V, 16 * kTbThreads), chunks = parts_of(H, 32 * kWave);
+    if (resample || chunks == 0 || (chunks >= segs && k >= 7) || (chunks >= 2 * segs && k >= 3)) return true;
+    const long weight = B * (4 * segs + chunks);
+    return k >= 7 ? weight <= 214 * (k + 4) : weight <= 162 * (k + 4) && B * (segs + chunks) <= 2 * kFill;
+}
+
 }  // namespace
 
 TreeBuildPlan tree_build_plan(int B, int S, int V, int H, int k) {
@@ -927,10 +962,6 @@ TreeBuildPlan tree_build_plan(int B, int S, int V, int H, int k) {
     // Tokens of a rows workgroup: 16 per thread, or 4 while that leaves CUs idle
     // (and needs no more than 32 segments). Columns of a step workgroup: 32 per
     // lane, or 16 likewise.
-    auto parts_of = [](long n, long per) {
-        const long x = (n + per - 1) / per;
-        return n <= 0 ? 0l : x > kMaxParts ? (long)kMaxParts : x;
-    };
     // Small ones only while a selection's keys stay 4 per lane (its instance with
     // 8 leaves room for one workgroup per CU).
     pl.kk = k <= 1 ? 1 : k <= 2 ? 2 : k <= 4 ? 4 : 8;
@@ -951,8 +982,8 @@ TreeBuildPlan tree_build_plan(int B, int S, int V, int H, int k) {
     // a multiple of 8 columns, for the wide table loads
     pl.chunk_len = chunks > 0 ? (int)((((long)H + chunks - 1) / chunks + 7) / 8 * 8) : 0;
     pl.max_nodes = 1 + k + (S - 1) * k * k;
-    // workspace: as many parts as any split of these sizes has, so that it does
-    // not grow for a smaller call
+    // workspace: as many parts as any split of these sizes has, and enough for
+    // either builder, so that it does not grow for a smaller call
     pl.row_parts = (size_t)rows * parts_of(V, 4 * kTbThreads);
     pl.col_parts = (size_t)B * k * parts_of(H, 16 * kWave);
     pl.frontier_bytes = (size_t)B * sizeof(TbFrontier);
@@ -970,7 +1001,7 @@ TreeBuildPlan tree_build_plan(int B, int S, int V, int H, int k) {
     add(nn * sizeof(int32_t));
     add(nn * sizeof(int32_t));
     add(nn * sizeof(double));
-    if (tree_build_many(k)) pl.bytes = std::max(pl.bytes, tree_build_many_bytes(B, S, V, H, k));
+    pl.bytes = std::max(pl.bytes, tree_build_many_bytes(B, S, V, H, k));
     return pl;
 }
 
@@ -981,12 +1012,7 @@ hipError_t launch_tree_build(const float *logits, const int32_t *root_token,
                              int32_t *token, float *joint, int32_t *num_nodes, void *workspace,
                              hipStream_t s) {
     if (B == 0) return hipSuccess;
-    // One wave per frontier node and one launch per step up to 8 branches. With
-    // more, nodes and selection would take two rounds per wave, and launches of
-    // their own win (tree_build_many.hip): k 10, 16 sequences 297 against 231 us, 4
-    // sequences of 32000 tokens 137 against 133, one without hot tokens 134 against
-    // 89; k 8, 16 sequences 158 against 199.
-    if (tree_build_many(k))
+    if (!one_launch_per_step(accept_len != nullptr, B, V, H, k))
         return launch_tree_build_many(logits, root_token, table, hot_vocab, hot_index, accept_len, r, B, S, V, H, k,
                                       budget, parent, token, joint, num_nodes, workspace, s);
     const TreeBuildPlan pl = tree_build_plan(B, S, V, H, k);

@@ -1,5 +1,5 @@
-// Draft-tree builder for more than 8 branches, for gfx950: the same trees as
-// tree_build.hip, with launches of their own for the rows of all steps
+// Draft-tree builder for large batches and for more than 8 branches, for gfx950:
+// the same trees as tree_build.hip, with launches of their own for the rows of all steps
 // (tb_rows_kernel, one streaming pass over the logits), each step's expansion
 // (tb_expand_kernel, one wave per frontier node and chunk of hot columns), its
 // selection (tb_select_kernel, one wave per frontier node) and the pruning
@@ -579,8 +579,6 @@ ManyPlan many_plan(int B, int S, int V, int H, int k) {
 }
 
 }  // namespace
-
-bool tree_build_many(int k) { return k > 8; }
 
 size_t tree_build_many_bytes(int B, int S, int V, int H, int k) {
     const ManyPlan pl = many_plan(B, S, V, H, k);

@@ -58,8 +58,7 @@ struct TreeBuildPlan {
 };
 TreeBuildPlan tree_build_plan(int B, int S, int V, int H, int k);
 
-// The builder for more than 8 branches (tree_build_many.hip).
-bool tree_build_many(int k);
+// The builder for large batches and more than 8 branches (tree_build_many.hip).
 size_t tree_build_many_bytes(int B, int S, int V, int H, int k);
 
 // Launch parameters of the tree-attention kernels (all sizes in elements).

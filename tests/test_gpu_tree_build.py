@@ -68,11 +68,15 @@ def test_tree_build_cases(oracle_mod, case):
 SPLITS = [
     # (B, S, V, H, k, budget): edges of the builder's splits
     (1, 2, 300000, 50, 3, 12),          # rows of more than one pass per segment
-    (1, 2, 8200, 1025, 9, 40),          # two segments and two chunks, both nearly empty; k above 8
-    (17, 2, 8193, 2056, 8, 30),         # two unequal chunks, wide table loads in one of them
-    (9, 3, 70000, 32769, 10, 60),       # 17 chunks of 32 columns per lane, rows not aligned
-    (3, 3, 4000, 4000, 16, 200),        # all hot, 16 branches: two rounds of nodes per wave
+    (1, 2, 8200, 1025, 9, 40),          # more than 8 branches: one segment, one chunk;
+    (17, 2, 8193, 2056, 8, 30),         # (8 branches: two unequal chunks)
+    (9, 3, 70000, 32769, 10, 60),       # five segments, 17 chunks, rows not aligned;
+    (3, 3, 4000, 4000, 16, 200),        # all hot, 16 branches
     (16, 2, 40000, 20001, 5, 20),       # odd hot count
+    (64, 2, 8200, 2056, 3, 12),         # two segments of 16 tokens per thread, two chunks of 32 columns per lane
+    (1, 2, 8200, 1025, 7, 40),          # five segments of 4 tokens per thread, two nearly empty chunks
+    (3, 3, 4000, 4000, 8, 200),         # all hot, 8 branches
+    (130, 2, 9000, 3000, 3, 12),        # more workgroups per step than run at once: separate launches
 ]
 
 
@@ -234,6 +238,17 @@ def test_tree_build_many_parts_list_overflow(oracle_mod):
     check_shared_row(oracle_mod, T, x, tab)
 
 
+@pytest.mark.parametrize("B,S,V,H,k", [
+    (9, 3, 70000, 32769, 6),   # 17 chunks of 32 columns per lane, rows not aligned
+    (1, 3, 70000, 66048, 4),   # chunks of two passes, wide table loads in both
+])
+def test_tree_build_wide_chunks(oracle_mod, B, S, V, H, k):
+    T = U.require_gpu()
+    print(f"case wide chunks B={B} V={V} H={H} k={k}", flush=True)
+    x, tab = shared_row_inputs(190 + k, B, S, V, H, k, 60)
+    check_shared_row(oracle_mod, T, x, tab)
+
+
 def test_tree_build_narrative(oracle_mod):
     """The worked example of §5.2 (golden fixture) on the GPU."""
     T = U.require_gpu()
@@ -306,13 +321,15 @@ def test_tree_build_reuses_workspace(oracle_mod):
         np.testing.assert_array_equal(nn.cpu().numpy(), want[3])
 
 
-def test_tree_build_workspace_alignment(oracle_mod):
-    """Full expansion chunks load four columns per lane when the rows and the
-    caller's arrays are aligned for it; a workspace that is only 8-byte aligned
-    (the documented minimum), or a table and hot-id array one element off, take
-    the narrow loads and build the same trees."""
+@pytest.mark.parametrize("k", [4, 12])
+def test_tree_build_workspace_alignment(oracle_mod, k):
+    """The expansions load several columns per lane at once where the table (and,
+    in separate launches, as more than 8 branches take, the hot ids and the
+    workspace row) are aligned for it; a workspace that is only 8-byte aligned (the
+    documented minimum), or a table and hot-id array one element off, take the
+    narrow loads and build the same trees."""
     T = U.require_gpu()
-    x = W.make_tree_build_inputs("align", 23, B=2, S=3, V=5000, H=4096, k=4, budget=30)
+    x = W.make_tree_build_inputs("align", 23, B=2, S=3, V=5000, H=4096, k=k, budget=30)
     n = T.tree_build_workspace_size(x.B, x.S, x.V, x.H, x.k)
     ws = torch.empty(n + 16, dtype=torch.uint8, device="cuda")
     margins = []
@@ -448,11 +465,14 @@ def compare_resample(oracle_mod, T, x, bonus, alen, r, label):
     return got
 
 
-@pytest.mark.parametrize("case", range(3))
+@pytest.mark.parametrize("case", range(6))
 def test_resample_cases(oracle_mod, case):
+    """The fourth and fifth in separate launches (more than 8 branches); the last a
+    batch that a first tree would take to them."""
     T = U.require_gpu()
     B, S, V, H, k, budget, r = [(6, 5, 800, 200, 3, 30, 1), (8, 7, 5000, 1000, 8, 64, 2),
-                                (4, 16, 600, 0, 2, 40, 0)][case]
+                                (4, 16, 600, 0, 2, 40, 0), (6, 5, 3000, 800, 12, 60, 1),
+                                (5, 6, 900, 0, 9, 30, 0), (130, 4, 9000, 3000, 3, 20, 1)][case]
     x = W.make_tree_build_inputs(f"rs{case}", 200 + case, B=B, S=S, V=V, H=H, k=k, budget=budget)
     rng = np.random.default_rng(case)
     alen = rng.integers(0, S + 2, B).astype(np.int32)         # 0 .. S+1, every window kind
