@@ -205,13 +205,22 @@ int tree_verify_attention(const uint16_t *q, const uint16_t *k_tree, const uint1
     if (num_wg > max_wg) num_wg = max_wg;
     // Short units are not worth splitting: one workgroup per unit saves the merge
     // launch and the partials it reads, 3-4 us, for about 1.2 us per tile of a
-    // unit of at most 16 rows or of head size 64, and 2 us of the others. Measured
-    // (us per call, whole and split): 16 rows of 64, 4 tiles 10.5 and 12.6; 12 rows
-    // of 128, 4 tiles 13.0 and 14.2; 132 rows of 128, 3 tiles 14.5 and 16.4; 256
-    // rows, 3 tiles 14.9 and 15.0, 4 tiles 16.9 and 15.0.
+    // unit of at most 16 rows or of head size 64, and 2 us of the others. While the
+    // units leave CUs idle, long ones (several row blocks, or one-token pages of head
+    // size 128, each load a page) are split a tile sooner. Measured (us per call,
+    // whole and split): 16 rows of 64, 4 tiles 10.5 and 12.6; 16 rows of 128, 4 tiles
+    // 13.0 and 13.9, with one-token pages 64 units 14.4 and 13.8, 128 units 13.0 and
+    // 14.4; 132 rows of 128, 3 tiles 14.5 and 16.4; 256 rows of 128, 3 tiles 14.9 and
+    // 15.0, 4 tiles 16.9 and 15.0; 512 rows of 64, 4 tiles, 16 units 15.9 and 15.4;
+    // 1024 rows of 64, 4 tiles, 8 units 14.4 and 13.7; 2048 rows of 64, 4 tiles, 16
+    // units 18.8 and 17.3; 2048 rows of 128, 3 tiles, 16 units 20.0 and 18.8.
     const long units = (long)B * Hkv * s.row_blocks;
     const long unit_tiles = (hint_len + tv::kKeyTile - 1) / tv::kKeyTile + (N + tv::kKeyTile - 1) / tv::kKeyTile;
-    const bool whole = units <= max_wg && unit_tiles <= (s.rows <= 16 || D == 64 ? 4 : 3);
+    const bool small_pages = P < 1024 / (2 * D);
+    const bool sooner = D == 64          ? s.rows > 256 && units < 128
+                        : s.rows <= 16 ? small_pages && units < 128
+                                       : s.rows > 512 && units < 32;
+    const bool whole = units <= max_wg && unit_tiles <= (D == 64 || s.rows <= 16 ? 4 : 3) - (sooner ? 1 : 0);
     if (whole) num_wg = units;
 
     tv::AttnParams p;
@@ -227,7 +236,7 @@ int tree_verify_attention(const uint16_t *q, const uint16_t *k_tree, const uint1
     p.max_pages = max_pages; p.num_pages = num_pages;
     p.rows_per_block = s.rows_per_block;
     p.setup_tiles = kSetupTiles;
-    p.small_pages = P < 1024 / (2 * D) ? 1 : 0;
+    p.small_pages = small_pages ? 1 : 0;
     p.narrow = s.rows <= 16 ? 1 : 0;
     p.num_wg = (int)num_wg;
     p.whole_units = whole ? 1 : 0;

@@ -77,6 +77,8 @@ def test_small_shapes_all_outputs(oracle_mod, case):
     (2, 80, 32, 8, 128, (0, 64), [80, 7], None),      # two row blocks, one in the second sequence
     (3, 70, 16, 2, 128, (1, 64), [0, 70, 33], None),  # three row blocks, an empty sequence
     (2, 20, 8, 2, 128, (500, 900), None, 10),         # understated lengths: whole, though long
+    (1, 128, 16, 2, 64, (65, 128), None, None),       # few units of several row blocks: split at 4 tiles,
+    (1, 128, 16, 2, 64, (0, 64), None, None),         # whole at 3
 ])
 def test_units_taken_whole(oracle_mod, B, N, Hq, Hkv, D, L, nodes, hint):
     """Short units run one per workgroup without a merge; the bound of the lengths
