@@ -162,6 +162,62 @@ def test_lm_head_equal_rows_pick_lowest_id(oracle_mod):
     assert got[0].reshape(-1)[r] == min(low, win)
 
 
+@pytest.mark.parametrize("B", [1, 4])
+def test_lm_head_equal_rows_everywhere(B):
+    """The same for duplicates in every place that a kernel compares two values:
+    64 rows take the weight's stream, 256 the tiled product. A hidden row is the
+    head row it ties on (so that its logit there is the maximum by far), and the
+    copy lies further on by: a value of the same lane, a lane of the other half,
+    another 16- or 32-row block, another wave, another workgroup, another tile of
+    the same workgroup. The last row's maximum is the last entry of a vocabulary
+    that is no multiple of a tile."""
+    T = U.require_gpu()
+    V, d, N = 76777, 64, 64                # 300 tiles of 256: workgroups 0..43 have two
+    print(f"case ties everywhere B={B} V={V}", flush=True)
+    rng = np.random.default_rng(B)
+    w = W.f32_to_bf16_bits(rng.standard_normal((V, d), dtype=np.float32))
+    h = W.f32_to_bf16_bits(rng.standard_normal((B * N, d), dtype=np.float32))
+    offs = (1, 2, 4, 8, 16, 32, 64, 128, 256, 300, 2048, 65536)
+    want = {}
+    for i, off in enumerate(offs):
+        for rep in range(4):               # in different rows of the block and of the tile
+            r = (i * 4 + rep) * B + rep % B
+            v = 256 * (i * 3 % 40) + 61 * rep + 5 * i
+            w[v + off] = w[v]
+            h[r] = w[v]
+            want[r] = v
+    last = B * N - 1
+    h[last] = w[V - 1]
+    want[last] = V - 1
+    rows = np.array(list(want))
+    assert len(rows) == 4 * len(offs) + 1
+    par = np.tile(np.arange(-1, N - 1, dtype=np.int32), (B, 1))
+    am, *_ = T.tree_lm_head_argmax_accept(U.dev_bf16(h.reshape(B, N, d)), U.dev_bf16(w),
+                                          U.dev(np.zeros((B, N), np.int32)), U.dev(par))
+    torch.cuda.synchronize()
+    exact = W.bf16_bits_to_f32(h[rows]).astype(np.float64) @ W.bf16_bits_to_f32(w).astype(np.float64).T
+    np.testing.assert_array_equal(exact.argmax(1), list(want.values()))
+    np.testing.assert_array_equal(am.cpu().numpy().reshape(-1)[rows], list(want.values()))
+
+
+def test_lm_head_longest_rows_in_blocks():
+    """A hidden size from 2^23 on takes the weight's stream for any number of
+    rows, 128 rows per launch. Every hidden row is a head row, whose logit is
+    above the others' by a factor of about sqrt(d)."""
+    T = U.require_gpu()
+    B, N, V, d = 3, 100, 200, 1 << 23
+    print(f"case longest rows R={B * N} V={V} d={d}", flush=True)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(5)
+    w = torch.randn((V, d), generator=g, device="cuda", dtype=torch.bfloat16)
+    pick = torch.randint(0, V, (B * N,), generator=g, device="cuda")
+    h = w[pick].view(B, N, d)
+    par = torch.arange(-1, N - 1, device="cuda", dtype=torch.int32).repeat(B, 1).contiguous()
+    am, *_ = T.tree_lm_head_argmax_accept(h, w, torch.zeros((B, N), dtype=torch.int32, device="cuda"), par)
+    torch.cuda.synchronize()
+    assert am.reshape(-1).tolist() == pick.tolist()
+
+
 def test_lm_head_tiled_special_values(oracle_mod):
     """The tiled product's search for the lowest entry of the maximum: a hidden
     row of zeros ties every entry at 0 (entry 0 wins), two infinite logits tie
