@@ -163,10 +163,20 @@ CALL_KERNELS = {
     "tree_verify_attention": ("tree_attention_kernel", "tree_attention_merge_kernel"),
     "tree_argmax_accept": ("argmax_segments_kernel", "accept_kernel"),
     "kv_compact_accepted": ("kv_compact_kernel",),
-    "tree_build": ("tb_finish_kernel", "tb_step_kernel", "tb_rows_kernel"),
+    "tree_build": ("tb_finish_kernel", "tb_prune_kernel", "tb_step_kernel", "tb_rows_kernel",
+                   "tb_expand_kernel", "tb_select_kernel"),
     "tree_lm_head_argmax_accept": ("lm_keys_clear_kernel", "lm_head_argmax_kernel",
                                    "lm_head_stream_kernel", "accept_kernel"),
 }
+
+
+def builder_launches(x) -> int:
+    """Launches of one builder call at the presets' sizes: one per step and the
+    finish up to 8 branches (the rows and the finish without hot tokens); above,
+    the rows, each step's expansion (with hot tokens) and selection, the pruning."""
+    if x.k <= 8:
+        return x.S + 1 if x.H else 2
+    return (2 * x.S if x.H else x.S) + 2
 
 
 def _counter_means(run_dir: str, counter: str):
@@ -203,7 +213,7 @@ def write_traffic(workload: str, fetch_dir: str, write_dir: str, copy_fetch_dir:
     for call, kernels in CALL_KERNELS.items():
         per = {}
         total = 0.0
-        calls = len(fv.get(kernels[0], []))          # the first kernel runs once per call
+        calls = next((len(fv[k]) for k in kernels if k in fv), 0)    # the first that runs does once per call
         for k in kernels:
             if k not in fv or k not in wv or calls == 0:
                 continue
@@ -390,7 +400,7 @@ def run_tree_build(args, T, torch):
                      "unit": "GB/s", "frac": round(ach / HBM_PEAK_GBS, 4),
                      "traffic": load_traffic("tree_build", args.workload), "kernel": "tree_build",
                      "avg_us": round(t_call.mean() * 1e6, 2), "algorithmic_bytes": int(nbytes),
-                     "launches_per_call": (2 if x.H == 0 else x.S + 1) if x.k <= 8 else 2 * x.S + 2},
+                     "launches_per_call": builder_launches(x)},
         "call_us_p10_p50_p90": [pct(t_call, 10), pct(t_call, 50), pct(t_call, 90)],
         "warmup_steps_run": warm_steps,
         "timed_steps_with_events": len(sampled),

@@ -424,9 +424,12 @@ __global__ __launch_bounds__(kLmThreads, 1) void lm_head_argmax_kernel(
 //   * The best key per hidden row stays in registers over the tiles: one atomic
 //     maximum per row and workgroup.
 // Every vocabulary row is summed in the same K order, so equal weight rows give
-// equal sums. Measured, this kernel against the 256-row tile (us, d = 4096):
-// 24 rows x 32000 entries 108 -> 47 (5.6 TB/s of weight), 64 x 128256
-// 269 -> 155 (6.8 TB/s), 64 x 50257 109 -> 77, 100 x 128256 266 -> 173.
+// equal sums. The time depends on the memory that a weight was given: between
+// buffers of one size and process it differs by up to a fifth. Measured per call
+// (three buffers each; us, d = 4096), this kernel against the 256-row tile: 24 rows
+// x 32000 entries 51 against 80 (the kernel alone 45-54, 4.9-5.8 TB/s of weight), 64 x
+// 128256 177-213 against 247-252 (alone 152-219, 4.8-6.9 TB/s), 64 x 50257 79-84
+// against 99-120, 100 x 128256 191-220 against 248-260.
 template <int NB, int MB, int S, int WV>
 __global__ __launch_bounds__(WV * kWave, 1) void lm_head_stream_kernel(
     const uint16_t *__restrict__ hidden, const uint16_t *__restrict__ w, int R, int V, int d,
@@ -604,20 +607,25 @@ hipError_t launch_stream(int groups, const uint16_t *hidden, const uint16_t *w, 
 }
 
 // Which split of the vocabulary the weight stream takes, by the rows a CU gets
-// (V / 256). us at d = 4096 unless stated, 64 rows or 24 rows:
+// (V / 256). us per call at d = 4096 unless stated, both sides on the same weights,
+// three buffers each:
 //   * V >= 98304 (384 rows per CU, at least 1.5 tiles of 256): one workgroup of
 //     8 waves x 32 rows per CU; the taller tile re-reads the hidden rows half as
-//     often (V = 128256: 155 against 179 with 16 rows per wave, 204 with two
-//     workgroups per CU; V = 75000, d = 2048: 77 against 71 with the next one).
-//   * 40960 <= V: two workgroups of 8 waves x 16 rows per CU (V = 50257: 77
-//     against 87-89 with one workgroup per CU).
+//     often (V = 128256, 64 rows: 177-213 against 198-218 with 16 rows per wave and
+//     202-207 with two workgroups per CU, 24 rows 173-202 against 193-210 and
+//     194-199; V = 98304 143-170 against 144-158 with the next one; V = 75000, d =
+//     2048: 74-83 against 72-78).
+//   * 40960 <= V: two workgroups of 8 waves x 16 rows per CU (V = 50257, 64 rows:
+//     79-84 against 86-97 with one workgroup per CU, 80-96 with 32 rows per wave).
 //   * 24576 <= V and d >= 2048: two workgroups of 4 waves x 16 rows per CU, a
-//     range of at most 80 rows each (V = 32000, 24 rows: 47 against 55-57).
+//     range of at most 80 rows each (V = 32000, 24 rows: 51 against 57-60, 64 rows 60
+//     against 62-63).
 //   * below, or with a short K loop, starting 512 workgroups costs more than
-//     their overlap gains: one workgroup of 8 waves x 16 rows per CU (V = 12000,
-//     d = 1024: 11 against 15; V = 32000, d = 1024: 15 against 18).
+//     their overlap gains: one workgroup of 8 waves x 16 rows per CU (24 rows, d =
+//     1024: V = 12000 17 against 20, V = 32000 20 against 23).
 // More than 64 rows: the hidden units fill the ring, one workgroup per CU; 32
-// rows per wave halve its LDS reads of them (V = 128256: 173 against 202-211).
+// rows per wave halve its LDS reads of them (100 rows: V = 128256 191-220 against
+// 214-227, V = 50257 87-102 against 99-108).
 hipError_t launch_stream_rows(const uint16_t *hidden, const uint16_t *w, int R, int V, int d,
                               unsigned long long *keys, hipStream_t s) {
     if (R > 64) return launch_stream<8, 2, 3, 8>(256, hidden, w, R, V, d, keys, s);

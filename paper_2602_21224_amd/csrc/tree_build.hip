@@ -17,7 +17,9 @@
 //     step, which the next launch needs.
 // tb_finish_kernel selects the last step's children and keeps the `budget`
 // nodes of largest joint probability, in creation order. Without hot tokens
-// only the rows (tb_rows_kernel) and tb_finish_kernel run.
+// only the rows (tb_rows_kernel) and tb_finish_kernel run. More than 8 branches,
+// and first trees of large batches, take tree_build_many.hip's separate launches
+// (one_launch_per_step).
 //
 // Decisions: candidates are ranked by the fp32 sum l + r (the precision of the
 // logits; ties to the lower vocabulary id) through a packed 64-bit key; -inf and
@@ -961,9 +963,15 @@ TreeBuildPlan tree_build_plan(int B, int S, int V, int H, int k) {
     const long rows = (long)B * S;
     // Tokens of a rows workgroup: 16 per thread, or 4 while that leaves CUs idle
     // (and needs no more than 32 segments). Columns of a step workgroup: 32 per
-    // lane, or 16 likewise.
-    // Small ones only while a selection's keys stay 4 per lane (its instance with
-    // 8 leaves room for one workgroup per CU).
+    // lane, or 16 likewise. Measured (us, 5 steps, small against large): tokens, 32000
+    // and none hot, k 8, 3 sequences 29.8 against 31.9, but k 4, 12 sequences 30.8
+    // against 28.8 (with hot tokens a step does not wait for its rows: no
+    // difference); columns, 32000 tokens all hot, k 4, 3 sequences 54 against 60, 6
+    // 60 against 67; 128256 tokens, 8192 hot, k 8, 6 sequences 71 against 80, but
+    // 32768 hot, k 4, 6 sequences 79 against 75.
+    // Small ones only while a selection's keys stay 4 per lane, so that one instance
+    // has 8. (With small parts and 8 keys: 128256 tokens, 32768 hot, k 8, 1 sequence
+    // 74 -> 65, 3 84 -> 73, 6 84 -> 87.)
     pl.kk = k <= 1 ? 1 : k <= 2 ? 2 : k <= 4 ? 4 : 8;
     const bool small_r = (long)B * parts_of(V, 16 * kTbThreads) < kFill / 2 && (long)V <= 4l * kTbThreads * kMaxParts;
     const bool small_c = (long)B * parts_of(H, 32 * kWave) < kFill / 2 && (long)H <= 16l * kWave * kMaxParts;
