@@ -168,6 +168,8 @@ CALL_KERNELS = {
     "tree_lm_head_argmax_accept": ("lm_keys_clear_kernel", "lm_head_argmax_kernel",
                                    "lm_head_stream_kernel", "accept_kernel"),
 }
+# kernels that run once per call; of the others a call's first one is
+ONCE_PER_CALL = {"tree_build": ("tb_finish_kernel", "tb_prune_kernel")}
 
 
 def builder_launches(x) -> int:
@@ -213,7 +215,7 @@ def write_traffic(workload: str, fetch_dir: str, write_dir: str, copy_fetch_dir:
     for call, kernels in CALL_KERNELS.items():
         per = {}
         total = 0.0
-        calls = next((len(fv[k]) for k in kernels if k in fv), 0)    # the first that runs does once per call
+        calls = max(len(fv.get(k, [])) for k in ONCE_PER_CALL.get(call, kernels[:1]))
         for k in kernels:
             if k not in fv or k not in wv or calls == 0:
                 continue

@@ -940,20 +940,24 @@ long parts_of(long n, long per) {
 //   16 + 16 (128256 tokens, 32768 hot), k 8: 16 sequences 154 / 186, 32 275 / 295;
 //     k 4: 32 sequences 237 / 229; k 2: 8 sequences 97 / 106, 16 136 / 129, 32 234 / 203;
 //   19 + 16 (151936, 32768), k 4: 8 sequences 120 / 123, 16 181 / 153;
-//   16 + 4 (128256, 8192), k 4: 16 sequences 108 / 119, 24 156 / 131; k 8: 16 117 / 146,
-//     64 286 / 236.
+//   16 + 4 (128256, 8192), k 4: 16 sequences 108 / 119, 24 156 / 131; k 8: 16
+//     117 / 146, 64 286 / 236.
 // Where the chunks are most of it (all of 32000 tokens hot: 4 + 16), or with 7 and 8
 // branches as many, separate launches pass over them too often: k 4, 32 sequences
-// 147 / 158, 64 232 / 272; 16 + 16, k 8, 64 sequences 475 / 503. And
+// 147 / 158, 64 232 / 272; 16 + 16, k 8, 64 sequences 475 / 503. (The first step has
+// one node to expand, which costs separate launches little: with one or two steps
+// only up to two rounds of workgroups; 16 + 16, k 8, 64 sequences, 2 steps 1.10 times.) And
 // re-sampled trees use one launch per step: separate launches reduce the rows of
 // the accepted positions too and cannot tell how many steps remain (32 sequences of
 // 128256 tokens, 32768 hot, k 4, 1 to 4 positions accepted: 187 / 226).
-bool one_launch_per_step(bool resample, int B, int V, int H, int k) {
+bool one_launch_per_step(bool resample, int B, int S, int V, int H, int k) {
     if (k > kMaxBranches) return false;
     const long segs = parts_of(V, 16 * kTbThreads), chunks = parts_of(H, 32 * kWave);
-    if (resample || chunks == 0 || (chunks >= segs && k >= 7) || (chunks >= 2 * segs && k >= 3)) return true;
-    const long weight = B * (4 * segs + chunks);
-    return k >= 7 ? weight <= 214 * (k + 4) : weight <= 162 * (k + 4) && B * (segs + chunks) <= 2 * kFill;
+    const long wgs = B * (segs + chunks), weight = B * (4 * segs + chunks);
+    if (resample || chunks == 0) return true;
+    if (((chunks >= segs && k >= 7) || (chunks >= 2 * segs && k >= 3)) && (S >= 3 || wgs <= 4 * kFill)) return true;
+    if (k >= 7) return weight <= 214 * (k + 4);
+    return 2 * chunks < segs ? wgs <= 440 : wgs <= 2 * kFill && weight <= 200 * (k + 4);
 }
 
 }  // namespace
@@ -1020,7 +1024,7 @@ hipError_t launch_tree_build(const float *logits, const int32_t *root_token,
                              int32_t *token, float *joint, int32_t *num_nodes, void *workspace,
                              hipStream_t s) {
     if (B == 0) return hipSuccess;
-    if (!one_launch_per_step(accept_len != nullptr, B, V, H, k))
+    if (!one_launch_per_step(accept_len != nullptr, B, S, V, H, k))
         return launch_tree_build_many(logits, root_token, table, hot_vocab, hot_index, accept_len, r, B, S, V, H, k,
                                       budget, parent, token, joint, num_nodes, workspace, s);
     const TreeBuildPlan pl = tree_build_plan(B, S, V, H, k);
