@@ -278,7 +278,7 @@ __device__ __forceinline__ void reduce_row(RowsShared &sh, const float *__restri
             fl = fminf(fl, s_gm[g]);
         }
         if (pm == kNegInf) continue;                 // uniform: no candidate in this pass
-        fl = fmaxf(fl, -__FLT_MAX__);                // -inf is no candidate
+        fl = fmaxf(k == 1 ? pm : fl, -__FLT_MAX__);  // -inf is no candidate
         double ps = 0.0;
         #pragma unroll
         for (int u = 0; u < U; ++u) ps += exp_nonpos((double)xv[u] - (double)pm, s_exp2);
@@ -683,7 +683,7 @@ __global__ __launch_bounds__(kTbThreads, 4) void tb_step_kernel(StepArgs p) {
             const float pm = wave_allmax(lm);
             const bool more = p0 > c0;
             if (pm == kNegInf) continue;             // wave-uniform: no candidate
-            const float fl = fmaxf(wave_floor(lm), -__FLT_MAX__);     // -inf is no candidate
+            const float fl = fmaxf(k == 1 ? pm : wave_floor(lm), -__FLT_MAX__);     // -inf is no candidate
             unsigned bits = 0u;
             #pragma unroll
             for (int u = 0; u < U; ++u) bits |= xv[u] >= fl ? 1u << u : 0u;
